@@ -33,6 +33,7 @@ COMMON = [
 SOURCES = {
     "api.cpp": ["-x", "hip"],
     "raster.hip": ["-ffp-contract=off"],
+    "rastermean.hip": ["-ffp-contract=off"],
     "conv.hip": [],
     "conv_ct.hip": [],
     "wiredirect.hip": [],

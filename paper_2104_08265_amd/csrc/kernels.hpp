@@ -29,15 +29,15 @@ struct RasterGeom {
 
 // Control words at the head of the raster workspace.
 enum RasterCtrl {
-  kCtrlHead = 0,    // work-queue head of the tile kernel
   kCtrlNItems = 1,  // number of tile work items
   kCtrlNBig = 2,    // rows whose window covers more than 4 tiles
   kCtrlTotal = 3,   // total (row, tile) pairs
-  kCtrlHeadZero = 4,  // queue head of the groups of tiles the tile kernel clears
-  kCtrlWords = 64
+  kCtrlHeads = 64,  // the tile kernel's kQueues work-queue heads, kQueueStride words apart
+  kCtrlWords = 64 + 8 * 32
 };
+constexpr int kQueues = 8, kQueueStride = 32;  // one queue per XCD, each head on its own 128-byte line
 constexpr int kRowsPerItem = 256;  // rows one tile work item processes at most
-constexpr int kZeroGroup = 16;     // tiles per clearing item of the tile kernel
+constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kernels at most
 constexpr int kScanPerBlock = 4096;
 
 // Raster tile variants: X(real type, TH rows, TW ticks, tile-kernel blocks per CU).
@@ -130,6 +130,10 @@ template <typename T>
 hipError_t launch_raster(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed,
                          T* grid, const RasterWs& ws, const DetTables* tables, const double* lfact, int n_cu,
                          hipStream_t st, ProfHook* prof, int tile);
+// rastermean.hip: the mean raster's tile kernel (the tiles binned, as launch_raster does).
+template <typename T, int TH, int TW>
+hipError_t launch_tile_mean(const DepoView<T>& d, const RasterGeom& g, double nsigma, T* grid, const RasterWs& ws,
+                            int n_cu, hipStream_t st);
 hipError_t launch_lfact_table(double* out, int n, const DetTables* tables, hipStream_t st);
 
 // drift.hip: 3D depositions -> depo-plane rows (plane-major, n_planes * n rows).

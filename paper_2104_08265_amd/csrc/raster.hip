@@ -10,19 +10,19 @@
 //  2. scan       - exclusive prefix sums give each tile its slice of a row list and
 //                  a number of work items (ceil(rows / kRowsPerItem); 0 for an empty tile);
 //  3. k_fill     - rows are written into their tiles' slices at their slots (plain stores);
-//  4. k_tile     - a persistent kernel takes, in step, a work item and a group of
-//                  kZeroGroup consecutive tiles from two atomic queues; a work item
-//                  accumulates its rows' in-tile sub-patches with LDS atomics and then
-//                  writes the tile: plain stores when the tile has one item, global atomic
-//                  adds when a crowded tile was split across items (those tiles are cleared
-//                  first by k_zero_split); a group's tiles that no row touches are cleared
-//                  with plain stores, so the grid needs no separate clearing.
+//  4. the tile kernel (rastermean.hip for the mean, k_tile for drawn counts) - persistent
+//                  blocks take work items from striped queues (next_item) and, in step, groups
+//                  of consecutive tiles to clear; a work item accumulates its rows' in-tile
+//                  sub-patches and then writes the tile: plain stores when the tile has one
+//                  item, global atomic adds when a crowded tile was split across items (those
+//                  tiles are cleared first by k_zero_split); a group's tiles that no row touches
+//                  are cleared with plain stores, so the grid needs no separate clearing.
 // Window bounds are formed in FP64 exactly as the oracle forms them, so both sides
 // agree on which cells a row touches; fluctuated counts use the deterministic
 // Philox + binomial chain of fluct.hpp (this file is compiled with contraction off).
 #include <type_traits>
 
-#include "kernels.hpp"
+#include "rasterwin.hpp"
 
 namespace wct {
 
@@ -30,60 +30,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-struct RowWin {
-  double q, u, su, t, st;
-  double ulo, uhi, tlo, thi;
-  int b0, b1, k0, k1;  // cell ranges clipped to the grid, [b0, b1) x [k0, k1)
-  int plane, event;  // event: slot in this call's grids (id - event_base)
-  int key_event;     // event id (fluctuation counter word 2)
-  bool ok;
-};
-
-__device__ __forceinline__ int clamp_idx(double v) {
-  v = fmin(fmax(v, -1.0e9), 1.0e9);
-  return (int)v;
-}
-
-template <typename T>
-__device__ __forceinline__ RowWin row_window(const DepoView<T>& d, int64_t j, const RasterGeom& g, double nsigma) {
-  RowWin w;
-  w.plane = d.plane ? d.plane[j] : 0;
-  w.key_event = d.event ? d.event[j] : 0;
-  w.event = w.key_event - g.event_base;
-  w.ok = w.plane >= 0 && w.plane < g.n_planes && w.key_event >= 0 && w.event >= 0 && w.event < g.n_events;
-  if (!w.ok) return w;
-  const PlaneGeom& pl = g.pl[w.plane];
-  w.q = (double)d.q[j];
-  const double p = (double)d.p[j];
-  const double sp = (double)d.sp[j];
-  w.t = (double)d.t[j];
-  w.st = (double)d.st[j];
-  w.ok = (w.q >= 0.0) && (w.st > 0.0) && (sp > 0.0) && isfinite(w.q) && isfinite(w.t) && isfinite(p) &&
-         isfinite(w.st) && isfinite(sp);
-  if (!w.ok) return w;
-  w.u = (double)pl.I * p;
-  w.su = (double)pl.I * sp;
-  const double hu = nsigma * w.su;
-  w.ulo = w.u - hu;
-  w.uhi = w.u + hu;
-  const double ht = nsigma * w.st;
-  w.tlo = w.t - ht;
-  w.thi = w.t + ht;
-  w.b0 = max(clamp_idx(floor(w.ulo)), 0);
-  w.b1 = min(clamp_idx(ceil(w.uhi)), pl.nb);
-  w.k0 = max(clamp_idx(floor(w.tlo)), 0);
-  w.k1 = min(clamp_idx(ceil(w.thi)), pl.nt);
-  w.ok = w.b0 < w.b1 && w.k0 < w.k1;
-  return w;
-}
-
-__device__ __forceinline__ int find_plane(const RasterGeom& g, int tin) {
-  int p = 0;
-  for (int k = 1; k < g.n_planes; ++k)
-    if (tin >= g.pl[k].tile_off) p = k;
-  return p;
 }
 
 // Erf at the cell edges of [k0, k1) for a window (lo, hi) around mu: edge 0 = max(k0, lo),
@@ -590,35 +536,6 @@ __global__ void k_items(const int32_t* __restrict__ item_off, int64_t ntiles, in
   for (int k = item_off[t]; k < item_off[t + 1]; ++k) items[k] = (int32_t)t;
 }
 
-// Writes zeros over tile t of the grid with the block's threads: 16-byte stores when the
-// tile's rows start on 16-byte boundaries, element stores otherwise.
-template <typename T, int TH, int TW>
-__device__ __forceinline__ void zero_tile(const RasterGeom& g, int64_t t, T* __restrict__ grid) {
-  constexpr int V = 16 / (int)sizeof(T);
-  static_assert(TW % V == 0, "tile width must be a whole number of 16-byte vectors");
-  const int ev = (int)(t / g.ntiles_ev);
-  const int tin = (int)(t - (int64_t)ev * g.ntiles_ev);
-  const PlaneGeom& pl = g.pl[find_plane(g, tin)];
-  const int tl = tin - pl.tile_off;
-  const int tr = tl / pl.ntc, tc = tl - (tl / pl.ntc) * pl.ntc;
-  const int tb0 = tr * TH, tk0 = tc * TW;
-  const int th = min(TH, pl.nb - tb0), tw = min(TW, pl.nt - tk0);
-  T* gp = grid + (int64_t)ev * g.grid_ev_stride + pl.grid_off + (int64_t)tb0 * pl.nt + tk0;
-  if (tw == TW && pl.nt % V == 0 && (reinterpret_cast<uintptr_t>(gp) & 15) == 0) {
-    constexpr int VR = TW / V;  // vectors per tile row
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int x = threadIdx.x; x < th * VR; x += blockDim.x) {
-      const int r = x / VR, c = x - (x / VR) * VR;
-      *reinterpret_cast<float4*>(gp + (int64_t)r * pl.nt + c * V) = z;
-    }
-  } else {
-    for (int x = threadIdx.x; x < th * TW; x += blockDim.x) {
-      const int r = x / TW, c = x - (x / TW) * TW;
-      if (c < tw) gp[(int64_t)r * pl.nt + c] = T(0);
-    }
-  }
-}
-
 // Tiles that several work items accumulate into start from zero.
 template <typename T, int TH, int TW>
 __global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, int64_t ntiles, T* __restrict__ grid) {
@@ -626,11 +543,10 @@ __global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, i
     if (counts[t] > kRowsPerItem) zero_tile<T, TH, TW>(g, t, grid);
 }
 
-// 4. persistent tile kernel -------------------------------------------------
-// Blocks take work from two queues in step: a tile work item (rows of one tile, added
-// in LDS and written out) and a group of kZeroGroup consecutive tiles, of which those no
-// row touches are cleared.  The clearing stores (HBM-bound) then overlap the arithmetic
-// of the rows instead of costing work items of their own.
+// 4. persistent tile kernel of the drawn counts --------------------------------
+// Blocks take a tile work item (rows of one tile, added in LDS and written out) and, in
+// step, a group of tiles to clear.  The clearing stores (HBM-bound) then overlap the
+// arithmetic of the rows instead of costing work items of their own.
 template <typename T, int MODE, int TH, int TW, int OCC>
 __global__ void __launch_bounds__(256, OCC) k_tile(DepoView<T> d, RasterGeom g, double nsigma, uint64_t seed,
                                               T* __restrict__ grid, const int32_t* __restrict__ list,
@@ -645,82 +561,35 @@ __global__ void __launch_bounds__(256, OCC) k_tile(DepoView<T> d, RasterGeom g, 
   __shared__ double s_ea[NWAVE][TH + 1];
   __shared__ double s_eb[NWAVE][TW + 1];
   __shared__ DetTablesSmall s_tb;
-  __shared__ int s_item, s_zero, s_row;
+  __shared__ int s_item, s_row;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (MODE == kModeBinomial) {
     for (int x = threadIdx.x; x < 129; x += blockDim.x) s_tb.inv[x] = tables->inv[x];
     for (int x = threadIdx.x; x < 19; x += blockDim.x) s_tb.fact[x] = tables->fact[x];
   }
   const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-  const int nzero = (int)((ntiles + kZeroGroup - 1) / kZeroGroup);
-  bool more_items = true, more_zero = true;  // block-uniform
-  for (;;) {
-    if (threadIdx.x == 0) {
-      s_item = more_items ? atomicAdd(&ctrl[kCtrlHead], 1) : INT_MAX;
-      s_zero = more_zero ? atomicAdd(&ctrl[kCtrlHeadZero], 1) : INT_MAX;
-    }
+  const int zgroup = zero_group(ntiles), nzero = (int)((ntiles + zgroup - 1) / zgroup);
+  const int nitems = ctrl[kCtrlNItems];
+  bool more_items = true;  // block-uniform
+  for (int step = 0;; ++step) {
+    if (threadIdx.x == 0) s_item = more_items ? next_item(ctrl, step == 0) : INT_MAX;
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep it scalar
-    const int zg = __builtin_amdgcn_readfirstlane(s_zero);
-    more_items = item < ctrl[kCtrlNItems];
-    more_zero = zg < nzero;
+    const int zg = (int)blockIdx.x + step * (int)gridDim.x;  // clearing groups are dealt out evenly
+    more_items = item < nitems;
+    const bool more_zero = zg < nzero;
     if (!more_items && !more_zero) break;
-    __syncthreads();  // every thread has read s_item and s_zero
+    __syncthreads();  // every thread has read s_item
     // the group is cleared after the item, so that its stores drain while the other
     // blocks of the CU compute
-    // With band hulls (wct_simulate), an empty tile outside its band's hull is left as it
-    // is: the row transform reads only inside the hulls.  The group's tiles are walked with
-    // their band and column stepped along (a band's hull is read once).
-    auto clear_group = [&]() {
-      if (!more_zero) return;
-      const int64_t t0 = (int64_t)zg * kZeroGroup, z1 = min(t0 + kZeroGroup, ntiles);
-      if (!hull) {
-        for (int64_t t = t0; t < z1; ++t)
-          if (counts[t] == 0) zero_tile<T, TH, TW>(g, t, grid);
-        return;
-      }
-      int ev = 0, p = 0, tr = 0, tc = 0;
-      int2 h = make_int2(0, 0);
-      auto locate = [&](int64_t t) {  // band, column and hull of tile t
-        ev = (int)(t / g.ntiles_ev);
-        const int tin = (int)(t - (int64_t)ev * g.ntiles_ev);
-        p = find_plane(g, tin);
-        const int tl = tin - (int)g.pl[p].tile_off;
-        tr = tl / g.pl[p].ntc;
-        tc = tl - tr * g.pl[p].ntc;
-        h = hull[(int64_t)ev * bands_before(g, g.n_planes) + bands_before(g, p) + tr];
-      };
-      locate(t0);
-      for (int64_t t = t0; t < z1; ++t) {
-        if (counts[t] == 0 && h.y > 0 && tc >= kSpanBase - h.x && tc < h.y) zero_tile<T, TH, TW>(g, t, grid);
-        if (++tc == g.pl[p].ntc) {  // next band (of this plane, or the next plane or event)
-          if (tr + 1 < g.pl[p].ntr) {
-            tc = 0;
-            ++tr;
-            h = hull[(int64_t)ev * bands_before(g, g.n_planes) + bands_before(g, p) + tr];
-          } else if (t + 1 < z1) {
-            locate(t + 1);
-          }
-        }
-      }
-    };
     if (!more_items) {
-      clear_group();
+      clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
       continue;
     }
-    const int t = items[item];
-    const int chunk = item - item_off[t];
-    const bool owned = (item_off[t + 1] - item_off[t]) == 1;
-    const int ev = t / g.ntiles_ev;
-    const int tin = t - ev * g.ntiles_ev;
-    const int pi = find_plane(g, tin);
+    const TileItem w_ = tile_item<TH, TW>(g, item, items, item_off, offs);
+    const int ev = w_.ev, pi = w_.plane, tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
+    const bool owned = w_.owned;
     const PlaneGeom& pl = g.pl[pi];
-    const int tl = tin - pl.tile_off;
-    const int tr = tl / pl.ntc, tc = tl - (tl / pl.ntc) * pl.ntc;
-    const int tb0 = tr * TH, tk0 = tc * TW;
-    const int th = min(TH, pl.nb - tb0), tw = min(TW, pl.nt - tk0);
-    const int r0 = offs[t] + chunk * kRowsPerItem;
-    const int r1 = min(offs[t] + (chunk + 1) * kRowsPerItem, offs[t + 1]);
     for (int x = threadIdx.x; x < TH * TW; x += blockDim.x) tile[x] = T(0);
     if (threadIdx.x == 0) s_row = r0;
     __syncthreads();
@@ -759,7 +628,7 @@ __global__ void __launch_bounds__(256, OCC) k_tile(DepoView<T> d, RasterGeom g, 
       }
     }
     __syncthreads();
-    clear_group();
+    if (more_zero) clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
   }
 }
 
@@ -878,9 +747,9 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
     WCT_TILE_LAUNCH(kModeBinomial);
   else if (mode == kModeNormal)
     WCT_TILE_LAUNCH(kModeNormal);
-  else
-    WCT_TILE_LAUNCH(kModeMean);
 #undef WCT_TILE_LAUNCH
+  if (mode == kModeMean) e = launch_tile_mean<T, TH, TW>(d, g, nsigma, grid, ws, n_cu, st);
+  if (e != hipSuccess) return e;
   WCT_CHECK_LAUNCH();
   if (prof) prof->end(st);
   if (prof) prof->begin("raster_wide_rows", st);
