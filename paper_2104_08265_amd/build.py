@@ -34,6 +34,7 @@ SOURCES = {
     "api.cpp": ["-x", "hip"],
     "raster.hip": ["-ffp-contract=off"],
     "rastermean.hip": ["-ffp-contract=off"],
+    "rasterdraw.hip": ["-ffp-contract=off"],
     "conv.hip": [],
     "conv_ct.hip": [],
     "wiredirect.hip": [],

@@ -13,6 +13,7 @@ namespace wct {
 // library's erf takes several times that and the fluctuation's series 100 to 240 operations.
 constexpr double kErfPolyNsigma = 4.2;
 constexpr double kErfPolyX = 8.820882;
+constexpr double kErfPolyEdge = 2.96999;  // below sqrt(X), above 4.2 / sqrt 2
 __host__ __device__ __forceinline__ double erf_poly(double x) {
   constexpr double c[23] = {0.47474863132061196, -0.23051951429446726, 0.15777328722547479,
                             -0.10925448496312597, 0.071094086262387321, -0.042370351732950742,

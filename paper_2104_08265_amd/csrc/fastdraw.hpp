@@ -1,0 +1,212 @@
+// Binomial and normal-approximation counts decided in FP32 wherever FP32 can decide them
+// (arXiv:2104.08265 Sec. 4.3.1).  The sampler of fluct.hpp defines every count as an FP64
+// computation; these functions return the same count from FP32 estimates of the same
+// quantities, or say that the estimates cannot tell (`sure` false): the caller then runs
+// the defining computation.  The counts are therefore those of fluct.hpp, bit for bit.
+//
+// A binomial count is the number of cumulative sums F(0), F(1), ... (in the order of the
+// search) that do not exceed the uniform u, so it is certain once u is further from every
+// sum than the estimates' error.  What the errors are, with e = 2^-24 (FP32 rounding):
+//  * p: the two FP64 weights rounded to FP32, their product, the division by N: 5 e
+//    relative, which moves a sum by at most N p pmf(k) 5 e <= 0.4 sqrt(N p) 5 e;
+//  * the first probability: inversion exp(N ln(1 - p)), an exponent of at most 14 (in
+//    base 2, 20) with 6 e relative error: 90 e; mode: a few e of a probability below 0.13;
+//  * each step's ratio: 6 e at most (the reciprocals of the hardware are within one unit
+//    in the last place); the sums weigh the k-th step's error by pmf(k): 6 e E[k] <= 60 e
+//    for the inversion, 6 e 0.8 sqrt(N p) for the search from the mode;
+//  * one rounding per subtraction from u: below e / 2 each, at most 30 that matter;
+//  * u: 26 of its 53 bits and one rounding: e.
+// Together below 190 e = 1.2e-5 for the inversion and 30 e + 8 e sqrt(N p) for the mode
+// search; the margins are 6e-5 and 6e-5 + 1.5e-6 sqrt(N p), five and three times that.
+// Random inputs leave 0.1 to 0.4% of the cells undecided.
+#pragma once
+
+#include <cmath>
+
+#include "fluct.hpp"
+
+namespace wct {
+
+WCT_HD float fast_rcp(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_rcpf(x);
+#else
+  return 1.0f / x;
+#endif
+}
+WCT_HD float fast_exp2(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_exp2f(x);
+#else
+  return exp2f(x);
+#endif
+}
+WCT_HD float fast_log2(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_logf(x);
+#else
+  return log2f(x);
+#endif
+}
+WCT_HD float fast_sqrt(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_sqrtf(x);
+#else
+  return sqrtf(x);
+#endif
+}
+
+constexpr float kDrawMargin = 6e-5f;        // what the sums must keep from u
+constexpr float kDrawMarginSigma = 1.5e-6f; // times sqrt(N p), for the search from the mode
+constexpr int kFastSteps = 126;             // inversion steps at most (even)
+constexpr int kFastPasses = 512;            // passes of the search from the mode at most
+constexpr float kFastMaxMean = 4096.0f;     // means up to which 512 passes hold eight widths
+constexpr float kFastMaxN = 67108864.0f;    // 2^26: above it the FP64 ln(n!) itself is only good to 1e-6
+
+// A cell surely draws 0 when u + N p is below this: 1 - N p is a lower bound of F(0), taken
+// with 1e-5 to spare.  Where p may exceed 1/2 the count runs down from N, not up from 0;
+// then N p >= 3/2 for three electrons or more, so only rows of one or two are kept out.
+WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : 1.0f - 1e-5f; }
+
+struct FastInv {
+  float v[kFastSteps + 2];
+};
+constexpr FastInv make_fast_inv() {
+  FastInv t{};
+  for (int j = 1; j < kFastSteps + 2; ++j) t.v[j] = 1.0f / (float)j;
+  return t;
+}
+constexpr FastInv kInvF = make_fast_inv();
+
+// Inversion from 0 (N p < 10).  The lanes of a wave step together until none searches.
+WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
+  const float mu = N * p;
+  const bool fits = (mu < kMuSwitch - 1e-4f) & (p < 0.4999f);
+  // -ln(1 - p) = 2 atanh(p / (2 - p))
+  const float s = p * fast_rcp(2.0f - p), s2 = s * s;
+  float poly = 1.0f / 13.0f;
+  poly = fmaf(poly, s2, 1.0f / 11.0f);
+  poly = fmaf(poly, s2, 1.0f / 9.0f);
+  poly = fmaf(poly, s2, 1.0f / 7.0f);
+  poly = fmaf(poly, s2, 1.0f / 5.0f);
+  poly = fmaf(poly, s2, 1.0f / 3.0f);
+  poly = fmaf(poly, s2, 1.0f);
+  float f = fast_exp2((N * s) * poly * (float)(-2.0 * kLog2e));
+  // f(k+1) = f(k) (r (N - k)) / (k + 1) = f(k) (r (N + 1) / (k + 1) - r)
+  const float r = p * fast_rcp(1.0f - p), c1 = fmaf(r, N, r);
+  float v = fits ? u - f : -1.0f;  // u - F(0); undecided cells do not search
+  float near = fabsf(v);
+  int k = v >= 0.0f ? 1 : 0;
+  for (int j = 1; j < kFastSteps; j += 2) {
+    if (!any_lane(v >= kDrawMargin)) break;
+    f *= fmaf(c1, kInvF.v[j], -r);
+    v -= f;
+    near = fminf(near, fabsf(v));
+    k += v >= 0.0f ? 1 : 0;
+    f *= fmaf(c1, kInvF.v[j + 1], -r);
+    v -= f;
+    near = fminf(near, fabsf(v));
+    k += v >= 0.0f ? 1 : 0;
+  }
+  *count = k;
+  return fits & (near >= kDrawMargin) & (v < 0.0f);
+}
+
+// (1 + e) ln(1 + e) - e over e^2, |e| <= 0.1
+WCT_HD float fast_dev(float e) {
+  float g = -1.0f / 42.0f;
+  g = fmaf(g, e, 1.0f / 30.0f);
+  g = fmaf(g, e, -1.0f / 20.0f);
+  g = fmaf(g, e, 1.0f / 12.0f);
+  g = fmaf(g, e, -1.0f / 6.0f);
+  return fmaf(g, e, 0.5f);
+}
+// ln(n!) less Stirling's n ln n - n + ln(2 pi n) / 2, from 1 / n, n >= 10
+WCT_HD float fast_stirling(float rn) {
+  const float r2 = rn * rn;
+  return rn * fmaf(-r2, fmaf(-r2, 1.0f / 1260.0f, 1.0f / 360.0f), 1.0f / 12.0f);
+}
+
+// The search from the mode (N p >= 10).  P(mode) by the saddle-point form: with
+// x = m - N p, ln P = S(N) - S(m) - S(N - m) - [N p h(x / N p) + N q h(-x / N q)]
+// - ln(2 pi m (N - m) / N) / 2, h(e) = (1 + e) ln(1 + e) - e, S the Stirling remainder:
+// no large terms cancel.
+WCT_HD bool fast_chopdown(float N, float p, float u, int* count) {
+  const float a = fmaf(N, p, p);  // (N + 1) p
+  const float m = floorf(a), fr = a - m, mu = a - p;
+  const float tol = 8e-7f * a;
+  const bool fits = (fr > tol) & (fr < 1.0f - tol) & (p < 0.4999f) & (mu > kMuSwitch + 1e-4f) & (mu < kFastMaxMean) &
+                    (N < kFastMaxN);
+  const float nm = N - m, nq = N - mu, q = 1.0f - p, x = p - fr;
+  const float rN = fast_rcp(N), rm = fast_rcp(m), rnm = fast_rcp(nm);
+  const float e1 = x * fast_rcp(mu), e2 = -x * fast_rcp(nq);
+  const float dev = x * (e1 * fast_dev(e1) - e2 * fast_dev(e2));
+  const float corr = fast_stirling(rN) - fast_stirling(rm) - fast_stirling(rnm) - dev;
+  const float pm = fast_exp2(corr * (float)kLog2e) * fast_sqrt(N * (rm * rnm) * 0.15915494f);
+  const float margin = fmaf(kDrawMarginSigma, fast_sqrt(m), kDrawMargin);
+  const float rp = p * fast_rcp(q), rq = q * fast_rcp(p);
+  float v = fits ? u - pm : -1.0f;
+  float near = fabsf(v), lo = pm, hi = pm;
+  float nlo = m * rq, dlo = nm + 1.0f;   // the next step's P ratio below the mode: nlo / dlo
+  float nhi = nm * rp, dhi = m + 1.0f;   // above: nhi / dhi
+  int c = v >= 0.0f ? 1 : 0;  // intervals (mode, below, above, below, ...) that u lies beyond
+  for (int j = 0; j < kFastPasses; ++j) {
+    if (!any_lane(v >= margin)) break;
+    const float rd = fast_rcp(dlo * dhi);
+    lo *= nlo * (rd * dhi);
+    hi *= nhi * (rd * dlo);
+    nlo = fmaxf(nlo - rq, 0.0f);  // 0 from the last step on: a lane whose search has ended
+    nhi = fmaxf(nhi - rp, 0.0f);  // keeps stepping beside the slower ones
+    dlo += 1.0f;
+    dhi += 1.0f;
+    v -= lo;
+    near = fminf(near, fabsf(v));
+    c += v >= 0.0f ? 1 : 0;
+    v -= hi;
+    near = fminf(near, fabsf(v));
+    c += v >= 0.0f ? 1 : 0;
+  }
+  *count = (int)m + ((c & 1) ? -((c + 1) >> 1) : (c >> 1));
+  return fits & (near >= margin) & (v < 0.0f);
+}
+
+// The normal mode's pair: z to within 1.3e-5 (the logarithm loses relative accuracy next to
+// u1 = 1, so pairs with u1 > 1 - 2^-10 are left to the defining computation).
+WCT_HD bool fast_normal_pair(uint32_t w0, uint32_t w1, uint32_t w2, float* z_even, float* z_odd) {
+  const uint32_t a = ~w0 >> 6, b = (1u << 27) - (w1 >> 5);
+  const float u1 = fmaf((float)a, 0x1p-26f, (float)b * 0x1p-53f);
+  const float r = fast_sqrt(fast_log2(u1) * (float)(-2.0 * kLn2));
+  const float f = (float)(w2 & 0x3fffffffu) * 0x1p-30f;
+  const bool swap = f > 0.5f;
+  const float t = (swap ? 1.0f - f : f) * (float)kHalfPi, t2 = t * t;
+  float s = 1.0f / 362880.0f;
+  s = fmaf(s, t2, -1.0f / 5040.0f);
+  s = fmaf(s, t2, 1.0f / 120.0f);
+  s = fmaf(s, t2, -1.0f / 6.0f);
+  s = fmaf(s * t2, t, t);
+  float c = -1.0f / 3628800.0f;
+  c = fmaf(c, t2, 1.0f / 40320.0f);
+  c = fmaf(c, t2, -1.0f / 720.0f);
+  c = fmaf(c, t2, 1.0f / 24.0f);
+  c = fmaf(c, t2, -0.5f);
+  c = fmaf(c, t2, 1.0f);
+  const float sp = swap ? c : s, cp = swap ? s : c;
+  const uint32_t j = w2 >> 30;
+  const float ze = (j & 1) ? sp : cp, zo = (j & 1) ? cp : sp;  // up to their signs
+  *z_even = r * ((j == 1 || j == 2) ? -ze : ze);
+  *z_odd = r * (j >= 2 ? -zo : zo);
+  return u1 <= 1.0f - 0x1p-10f;
+}
+
+// The normal mode's count: certain unless x = mu + sd z + 1/2 is within its error of a whole
+// number (mu: 6 e relative, sd: 4 e, z: 1.3e-5) or reaches the clamp at N.
+WCT_HD bool fast_normal_count(float N, float mu, float p, float z, int* count) {
+  const float sd = fast_sqrt(fmaxf(mu * (1.0f - p), 0.0f));
+  const float x = fmaf(sd, z, mu) + 0.5f;
+  const float fl = floorf(x), fr = x - fl;
+  const float margin = fmaf(sd, 3e-5f, fmaf(mu, 1e-6f, 2e-6f));
+  *count = (int)fmaxf(fl, 0.0f);
+  return ((fr > margin) & (fr < 1.0f - margin) & (x < N)) | (x < -margin);
+}
+
+}  // namespace wct

@@ -134,6 +134,11 @@ hipError_t launch_raster(const DepoView<T>& d, const RasterGeom& g, double nsigm
 template <typename T, int TH, int TW>
 hipError_t launch_tile_mean(const DepoView<T>& d, const RasterGeom& g, double nsigma, T* grid, const RasterWs& ws,
                             int n_cu, hipStream_t st);
+// rasterdraw.hip: the tile kernel of drawn counts (mode binomial or normal).
+template <typename T, int TH, int TW>
+hipError_t launch_tile_draw(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed, T* grid,
+                            const RasterWs& ws, const DetTables* tables, const double* lfact, int n_cu,
+                            hipStream_t st);
 hipError_t launch_lfact_table(double* out, int n, const DetTables* tables, hipStream_t st);
 
 // drift.hip: 3D depositions -> depo-plane rows (plane-major, n_planes * n rows).

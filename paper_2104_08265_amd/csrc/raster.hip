@@ -10,7 +10,7 @@
 //  2. scan       - exclusive prefix sums give each tile its slice of a row list and
 //                  a number of work items (ceil(rows / kRowsPerItem); 0 for an empty tile);
 //  3. k_fill     - rows are written into their tiles' slices at their slots (plain stores);
-//  4. the tile kernel (rastermean.hip for the mean, k_tile for drawn counts) - persistent
+//  4. the tile kernel (rastermean.hip for the mean, rasterdraw.hip for drawn counts) - persistent
 //                  blocks take work items from striped queues (next_item) and, in step, groups
 //                  of consecutive tiles to clear; a work item accumulates its rows' in-tile
 //                  sub-patches and then writes the tile: plain stores when the tile has one
@@ -72,7 +72,7 @@ __device__ __forceinline__ int div_small(int x, int d, float rd) {
 // A queue lives in registers: position e (< 128) is held by lane e & 63 in slot e >> 6.
 // A push moves each new entry to its lane with one ds_permute per 32-bit word; a run
 // takes slot 0 (positions 0..63) and slot 1 moves down.  The queues are emptied at the
-// end of every row's sub-patch, so a batch shares the row's electron count N (a
+// end of every chunk of a row, so a batch shares the row's electron count N (a
 // wave-uniform value: the sampler's power loop then runs under scalar control).
 
 __device__ __forceinline__ int lanes_below(uint64_t mask, int lane) {
@@ -135,57 +135,28 @@ __device__ __forceinline__ void rq_run(RegQueue& q, int take, int N, double lfN,
   q.n -= take;
 }
 
-// The chop-down queue may outlive a row: the tile kernel keeps one per wave for a whole
-// work item, so that its batches fill up across rows.  Its entries then carry their
-// row's electron count in the bits of the offset above kDstBits (tile offsets are below
-// 2^13); a count of 0 there stands for `rowN`, the count of the row being rasterised,
-// which is how rows with 2^19 or more electrons (and the wide-row kernel, whose offsets
-// need all the bits) enqueue: such a row empties the queue when it ends.
-constexpr int kDstBits = 13;
-constexpr int kPackN = 1 << (32 - kDstBits);
-
-template <typename T, typename Add>
-__device__ __forceinline__ void rq_run_chop(RegQueue& q, int take, int rowN, bool packed, int lane,
-                                            const DetTablesSmall& tb, const double* __restrict__ lf, Add add) {
-  if (lane < take) {
-    const uint32_t e = q.d0;
-    const int fieldN = packed ? (int)(e >> kDstBits) : 0;
-    const int N = fieldN ? fieldN : rowN;
-    const uint32_t d = packed ? (e & ((1u << kDstBits) - 1u)) : e;
-    const int k = binom_regime_draw<1>(N, lfact_of(N, lf, tb), q.p0, q.u0, tb, lf);
-    if (k) add(d, (T)k);
-  }
-  q.p0 = q.p1;
-  q.u0 = q.u1;
-  q.d0 = q.d1;
-  q.n -= take;
-}
-
 // A cell's outcome of the cheap tests: added at once, queued for its regime, or nothing.
-// `tagN` is what the chop-down entry carries (the row's count, or 0 for `rowN`).
 template <typename T, typename Add>
-__device__ __forceinline__ void cell_route(RegQueue& qi, RegQueue& qc, bool packed, int tagN, int quick,
-                                           double p, double u, int N, double lfN, uint32_t dst, int lane,
-                                           const DetTablesSmall& tb, const double* __restrict__ lf, Add add) {
+__device__ __forceinline__ void cell_route(RegQueue& qi, RegQueue& qc, int quick, double p, double u, int N,
+                                           double lfN, uint32_t dst, int lane, const DetTablesSmall& tb,
+                                           const double* __restrict__ lf, Add add) {
   if (quick > 0) add(dst, (T)quick);
   rq_push(qi, quick == -1, p, u, dst, lane);
   if (qi.n >= 64) rq_run<T, 0>(qi, 64, N, lfN, lane, tb, lf, add);
-  rq_push(qc, quick == -2, p, u, packed ? dst | ((uint32_t)tagN << kDstBits) : dst, lane);
-  if (qc.n >= 64) rq_run_chop<T>(qc, 64, N, packed, lane, tb, lf, add);
+  rq_push(qc, quick == -2, p, u, dst, lane);
+  if (qc.n >= 64) rq_run<T, 1>(qc, 64, N, lfN, lane, tb, lf, add);
 }
 
 // One wave rasterises the cells [b0, b1) x [k0, k1) of a row; `dst(b, k)` names a cell and
 // `add(dst, value)` accumulates a nonzero contribution.  Fluctuated cells are drawn in
 // tick pairs: cells (b, 2m), (b, 2m+1) share one Philox4x32-10 block (counter
 // b*ceil(N_t/2) + m), words 0-1 for the even tick and 2-3 for the odd one.
-// PACKED: `qc` is the caller's chop-down queue of a whole work item (entries carry their
-// count; the caller empties it at the item's end); otherwise it is emptied here.
-template <typename T, int MODE, bool PACKED, typename Dst, typename Add>
+template <typename T, int MODE, typename Dst, typename Add>
 __device__ __forceinline__ void patch_cells(const RowWin& w, int b0, int b1, int k0, int k1, int nt, uint32_t did,
                                             uint32_t ev, uint32_t plane, uint32_t key0, uint32_t key1,
                                             double* __restrict__ ea, double* __restrict__ eb,
                                             const DetTablesSmall& tb, const double* __restrict__ lf, int lane, Dst dst,
-                                            Add add, RegQueue& qc) {
+                                            Add add) {
   const int nbr = b1 - b0, nkr = k1 - k0;
   edge_fill2<MODE>(ea, b0, b1, w.u, w.su, w.ulo, w.uhi, eb, k0, k1, w.t, w.st, w.tlo, w.thi, lane);
   wave_sync();
@@ -226,9 +197,9 @@ __device__ __forceinline__ void patch_cells(const RowWin& w, int b0, int b1, int
     const int N = __builtin_amdgcn_readfirstlane((int)floor(fmin(w.q + 0.5, 2147483647.0)));
     if (N > 0) {
       const double lfN = lfact_of(N, lf, tb);
-      const int tagN = N < kPackN ? N : 0;  // 0: the entry stands for this row's count
-      RegQueue qi;
+      RegQueue qi, qc;
       qi.n = 0;
+      qc.n = 0;
       const int j0 = k0 >> 1, np = ((k1 - 1) >> 1) - j0 + 1;
       const uint32_t half_nt = (uint32_t)((nt + 1) >> 1);
       const float rd = 1.0f / (float)np;
@@ -257,12 +228,11 @@ __device__ __forceinline__ void patch_cells(const RowWin& w, int b0, int b1, int
             quick_o = binom_quick(N, po, uo);
           }
         }
-        cell_route<T>(qi, qc, PACKED, tagN, quick_e, pe, ue, N, lfN, de, lane, tb, lf, add);
-        cell_route<T>(qi, qc, PACKED, tagN, quick_o, po, uo, N, lfN, dodd, lane, tb, lf, add);
+        cell_route<T>(qi, qc, quick_e, pe, ue, N, lfN, de, lane, tb, lf, add);
+        cell_route<T>(qi, qc, quick_o, po, uo, N, lfN, dodd, lane, tb, lf, add);
       }
       if (qi.n > 0) rq_run<T, 0>(qi, qi.n, N, lfN, lane, tb, lf, add);
-      // entries that stand for this row's count cannot outlive it
-      if ((!PACKED || tagN == 0) && qc.n > 0) rq_run_chop<T>(qc, qc.n, N, PACKED, lane, tb, lf, add);
+      if (qc.n > 0) rq_run<T, 1>(qc, qc.n, N, lfN, lane, tb, lf, add);
     }
   }
   wave_sync();
@@ -543,95 +513,6 @@ __global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, i
     if (counts[t] > kRowsPerItem) zero_tile<T, TH, TW>(g, t, grid);
 }
 
-// 4. persistent tile kernel of the drawn counts --------------------------------
-// Blocks take a tile work item (rows of one tile, added in LDS and written out) and, in
-// step, a group of tiles to clear.  The clearing stores (HBM-bound) then overlap the
-// arithmetic of the rows instead of costing work items of their own.
-template <typename T, int MODE, int TH, int TW, int OCC>
-__global__ void __launch_bounds__(256, OCC) k_tile(DepoView<T> d, RasterGeom g, double nsigma, uint64_t seed,
-                                              T* __restrict__ grid, const int32_t* __restrict__ list,
-                                              const int32_t* __restrict__ offs, const int32_t* __restrict__ items,
-                                              const int32_t* __restrict__ item_off, const int32_t* __restrict__ counts,
-                                              int64_t ntiles, int32_t* __restrict__ ctrl,
-                                              const DetTables* __restrict__ tables, const double* __restrict__ lf,
-                                              const int2* __restrict__ hull) {
-  constexpr int NWAVE = 4;
-  static_assert(TH * TW <= (1 << kDstBits), "tile offsets must fit below the packed electron count");
-  __shared__ T tile[TH * TW];
-  __shared__ double s_ea[NWAVE][TH + 1];
-  __shared__ double s_eb[NWAVE][TW + 1];
-  __shared__ DetTablesSmall s_tb;
-  __shared__ int s_item, s_row;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (MODE == kModeBinomial) {
-    for (int x = threadIdx.x; x < 129; x += blockDim.x) s_tb.inv[x] = tables->inv[x];
-    for (int x = threadIdx.x; x < 19; x += blockDim.x) s_tb.fact[x] = tables->fact[x];
-  }
-  const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-  const int zgroup = zero_group(ntiles), nzero = (int)((ntiles + zgroup - 1) / zgroup);
-  const int nitems = ctrl[kCtrlNItems];
-  bool more_items = true;  // block-uniform
-  for (int step = 0;; ++step) {
-    if (threadIdx.x == 0) s_item = more_items ? next_item(ctrl, step == 0) : INT_MAX;
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep it scalar
-    const int zg = (int)blockIdx.x + step * (int)gridDim.x;  // clearing groups are dealt out evenly
-    more_items = item < nitems;
-    const bool more_zero = zg < nzero;
-    if (!more_items && !more_zero) break;
-    __syncthreads();  // every thread has read s_item
-    // the group is cleared after the item, so that its stores drain while the other
-    // blocks of the CU compute
-    if (!more_items) {
-      clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
-      continue;
-    }
-    const TileItem w_ = tile_item<TH, TW>(g, item, items, item_off, offs);
-    const int ev = w_.ev, pi = w_.plane, tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
-    const bool owned = w_.owned;
-    const PlaneGeom& pl = g.pl[pi];
-    for (int x = threadIdx.x; x < TH * TW; x += blockDim.x) tile[x] = T(0);
-    if (threadIdx.x == 0) s_row = r0;
-    __syncthreads();
-    auto dst = [&](int b, int k) { return (uint32_t)((b - tb0) * TW + (k - tk0)); };
-    auto add = [&](uint32_t o, T v) { atomicAdd(&tile[o], v); };
-    // the waves claim rows one at a time, so that they finish the item together
-    auto claim = [&]() {
-      int r = 0;
-      if (lane == 0) r = atomicAdd(&s_row, 1);
-      return __builtin_amdgcn_readfirstlane(r);
-    };
-    RegQueue qc;  // this wave's chop-down queue for the item
-    qc.n = 0;
-    for (int r = claim(); r < r1; r = claim()) {
-      // the row is wave-uniform: a scalar index makes its parameters scalar loads and registers
-      const int64_t j = __builtin_amdgcn_readfirstlane(list[r]);
-      const RowWin w = row_window(d, j, g, nsigma);
-      const int bb0 = max(w.b0, tb0), bb1 = min(w.b1, tb0 + th);
-      const int kk0 = max(w.k0, tk0), kk1 = min(w.k1, tk0 + tw);
-      if (!w.ok || bb0 >= bb1 || kk0 >= kk1) continue;
-      const uint32_t did = d.depo_id ? (uint32_t)d.depo_id[j] : (uint32_t)j;
-      patch_cells<T, MODE, true>(w, bb0, bb1, kk0, kk1, pl.nt, did, (uint32_t)w.key_event, (uint32_t)pi, key0, key1,
-                                  s_ea[wv], s_eb[wv], s_tb, lf, lane, dst, add, qc);
-    }
-    if (MODE == kModeBinomial && qc.n > 0) rq_run_chop<T>(qc, qc.n, 0, true, lane, s_tb, lf, add);
-    __syncthreads();
-    T* gp = grid + (int64_t)ev * g.grid_ev_stride + pl.grid_off;
-    for (int x = threadIdx.x; x < th * TW; x += blockDim.x) {
-      const int rr = x / TW, c = x - (x / TW) * TW;
-      if (c < tw) {
-        T* dst = gp + (int64_t)(tb0 + rr) * pl.nt + tk0 + c;
-        if (owned)
-          *dst = tile[x];
-        else if (tile[x] != T(0))
-          atomicAdd(dst, tile[x]);
-      }
-    }
-    __syncthreads();
-    if (more_zero) clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
-  }
-}
-
 // 5. rows wider than 4 tiles: 64 x 64 chunks per wave, straight to global atomics ------
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256, 3) k_big(DepoView<T> d, RasterGeom g, double nsigma, uint64_t seed,
@@ -666,10 +547,8 @@ __global__ void __launch_bounds__(256, 3) k_big(DepoView<T> d, RasterGeom g, dou
       const int cb = c / nck, ck = c - (c / nck) * nck;
       const int b0 = w.b0 + cb * CB, b1 = min(b0 + CB, w.b1);
       const int k0 = max(kstart + ck * CK, w.k0), k1 = min(kstart + (ck + 1) * CK, w.k1);
-      RegQueue qc;
-      qc.n = 0;
-      patch_cells<T, MODE, false>(w, b0, b1, k0, k1, pl.nt, did, (uint32_t)w.key_event, (uint32_t)w.plane, key0, key1,
-                                   s_ea[wv], s_eb[wv], s_tb, lf, lane, dst, add, qc);
+      patch_cells<T, MODE>(w, b0, b1, k0, k1, pl.nt, did, (uint32_t)w.key_event, (uint32_t)w.plane, key0, key1,
+                           s_ea[wv], s_eb[wv], s_tb, lf, lane, dst, add);
     }
   }
 }
@@ -689,7 +568,7 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
     if (e_ != hipSuccess) return e_;        \
   } while (0)
 
-template <typename T, int TH, int TW, int OCC>
+template <typename T, int TH, int TW>
 hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed,
                                T* grid, const RasterWs& ws, const DetTables* tables, const double* lfact, int n_cu,
                                hipStream_t st, ProfHook* prof) {
@@ -737,20 +616,13 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
   hipLaunchKernelGGL((k_zero_split<T, TH, TW>), dim3(1024), dim3(256), 0, st, g, ws.counts, nt, grid);
   WCT_CHECK_LAUNCH();
   if (prof) prof->end(st);
-  const unsigned pblocks = (unsigned)(n_cu * OCC);  // the blocks that fit a CU at once (LDS, registers)
   static const char* const kTileName[3] = {"raster_tile_mean", "raster_tile_fluct", "raster_tile_normal"};
   if (prof) prof->begin(kTileName[mode], st);
-#define WCT_TILE_LAUNCH(M)                                                                                        \
-  hipLaunchKernelGGL((k_tile<T, M, TH, TW, OCC>), dim3(pblocks), dim3(256), 0, st, d, g, nsigma, seed, grid, ws.list, \
-                     ws.offs, ws.items, ws.item_off, ws.counts, nt, ws.ctrl, tables, lfact, ws.hull)
-  if (mode == kModeBinomial)
-    WCT_TILE_LAUNCH(kModeBinomial);
-  else if (mode == kModeNormal)
-    WCT_TILE_LAUNCH(kModeNormal);
-#undef WCT_TILE_LAUNCH
-  if (mode == kModeMean) e = launch_tile_mean<T, TH, TW>(d, g, nsigma, grid, ws, n_cu, st);
+  if (mode == kModeMean)
+    e = launch_tile_mean<T, TH, TW>(d, g, nsigma, grid, ws, n_cu, st);
+  else
+    e = launch_tile_draw<T, TH, TW>(d, g, nsigma, mode, seed, grid, ws, tables, lfact, n_cu, st);
   if (e != hipSuccess) return e;
-  WCT_CHECK_LAUNCH();
   if (prof) prof->end(st);
   if (prof) prof->begin("raster_wide_rows", st);
 #define WCT_BIG_LAUNCH(M)                                                                                      \
@@ -778,7 +650,7 @@ hipError_t launch_raster(const DepoView<T>& d, const RasterGeom& g, double nsigm
 #define WCT_TILE_CASE(TT, TH_, TW_, OCC)                                                                    \
   if constexpr (std::is_same<T, TT>::value) {                                                              \
     if (id++ == tile)                                                                                      \
-      e = launch_raster_tiles<T, TH_, TW_, OCC>(d, g, nsigma, mode, seed, grid, ws, tables, lfact, n_cu,      \
+      e = launch_raster_tiles<T, TH_, TW_>(d, g, nsigma, mode, seed, grid, ws, tables, lfact, n_cu,      \
                                                 st, prof);                                                  \
   }
   WCT_TILE_VARIANTS(WCT_TILE_CASE)
