@@ -10,7 +10,7 @@
 // where 32-bit integer ones take 5.4 (measured, 256-thread blocks, any address pattern).  A
 // tile is therefore summed in 32-bit integers and converted when it is written; an item
 // whose electrons could overflow them adds to the grid directly.  Together: three-plane
-// event of 1e5 depositions 6.3 -> 4.0 ms, two-face showers of 1e6 depositions 37 -> 24 ms.
+// event of 1e5 depositions 6.3 -> 3.6 ms, two-face showers of 1e6 depositions 37 -> 21 ms.
 #include "erfpoly.hpp"
 #include "fastdraw.hpp"
 #include "rasterwin.hpp"
@@ -48,14 +48,58 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
+// Everything the kernel takes.  The out-of-line functions below get its address (the kernel
+// argument segment), so that calling them costs the kernel no registers.
+template <typename T>
+struct DrawArgs {
+  DepoView<T> d;
+  RasterGeom g;
+  double nsigma;
+  uint32_t key0, key1;
+  T* grid;
+  const int32_t *list, *offs, *items, *item_off, *counts;
+  int64_t ntiles;
+  int32_t* ctrl;
+  const DetTables* tables;
+  const double* lf;
+  const int2* hull;
+};
+
+// x ^ y ^ z, one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t x, uint32_t y, uint32_t z) {
+  return __builtin_amdgcn_bitop3_b32(x, y, z, 0x96);
+}
+
+// philox4x32_10 (fluct.hpp) with the round keys made by scalar adds where they are used
+// (kept across the loop over cells, the compiler spills the 20 of them).
+__device__ __forceinline__ Philox4 philox_cell(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
+                                               uint32_t k1) {
+  __asm__ volatile("" : "+s"(k0), "+s"(k1));
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    c1 = (uint32_t)p1;
+    c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+    c3 = (uint32_t)p0;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  return Philox4{c0, c1, c2, c3};
+}
+
 __device__ __forceinline__ float electrons_of(double q) { return (float)floor(fmin(q + 0.5, 2147483647.0)); }
 
 // The defining computation of one cell's count (lanes may hold cells of different rows).
+// Out of line, like the erf series: inlined, the FP64 constants of both cost the loop over
+// cells about 470 spilled scalar registers.
 template <typename T, int MODE>
-__device__ __forceinline__ int exact_count(const DepoView<T>& d, const RasterGeom& g, double nsigma, uint32_t key0,
-                                           uint32_t key1, int64_t j, int b, int k, const DetTables& tb,
-                                           const double* __restrict__ lf) {
-  const RowWin w = row_window(d, j, g, nsigma);
+__device__ __attribute__((noinline)) int exact_count(const DrawArgs<T>* args, int64_t j, int b, int k) {
+  const DepoView<T>& d = args->d;
+  const RasterGeom& g = args->g;
+  const DetTables& tb = *args->tables;
+  const double* __restrict__ lf = args->lf;
+  const RowWin w = row_window(d, j, g, args->nsigma);
   if (!w.ok || b < w.b0 || b >= w.b1 || k < w.k0 || k >= w.k1) return 0;
   const double s2a = w.su * kSqrt2, s2b = w.st * kSqrt2;
   double e[4];
@@ -74,7 +118,7 @@ __device__ __forceinline__ int exact_count(const DepoView<T>& d, const RasterGeo
   const uint32_t did = d.depo_id ? (uint32_t)d.depo_id[j] : (uint32_t)j;
   const uint32_t half_nt = (uint32_t)((g.pl[w.plane].nt + 1) >> 1);
   const Philox4 ph = philox4x32_10((uint32_t)b * half_nt + (uint32_t)(k >> 1), did, (uint32_t)w.key_event,
-                                   (uint32_t)w.plane << 24, key0, key1);
+                                   (uint32_t)w.plane << 24, args->key0, args->key1);
   if (MODE == kModeNormal) {
     double ze, zo;
     box_muller_pair(ph, &ze, &zo);
@@ -87,6 +131,8 @@ __device__ __forceinline__ int exact_count(const DepoView<T>& d, const RasterGeo
                      : binom_regime_draw<1>(N, lfact_of(N, lf, tb), p, u, tb, lf);
 }
 
+__device__ __attribute__((noinline)) double det_erf_call(double x) { return det_erf(x); }
+
 // A row's weights on the tile's cells [b0, b1) x [k0, k1) into LDS: impact weights times
 // `scale`, tick weights from slot k0 & 1 on (slots of a tick pair side by side, ticks
 // outside the window 0).  A lane holds one edge of either axis and takes the upper edge of
@@ -95,7 +141,7 @@ __device__ __forceinline__ int exact_count(const DepoView<T>& d, const RasterGeo
 __device__ __forceinline__ void row_weights(const RowWin& w, int b0, int b1, int k0, int k1, float scale,
                                             float* __restrict__ wa, float* __restrict__ wb, int lane) {
   const int na = b1 - b0, nb = k1 - k0, odd = k0 & 1;
-  const double s2a = w.su * kSqrt2, s2b = w.st * kSqrt2;
+  const double s2a = w.su * kSqrt2, s2b = w.st * kSqrt2, ra = 1.0 / s2a, rb = 1.0 / s2b;
   if (lane == 0) {
     wb[0] = 0.0f;
     wb[(odd + nb - 1) | 1] = 0.0f;
@@ -107,10 +153,10 @@ __device__ __forceinline__ void row_weights(const RowWin& w, int b0, int b1, int
     const int i = min(a ? x : x - (na + 1), a ? na : nb);
     const double at = (double)((a ? b0 : k0) + i);
     const double edge = fmin(fmax(at, a ? w.ulo : w.tlo), a ? w.uhi : w.thi);
-    const double z = (edge - (a ? w.u : w.t)) / (a ? s2a : s2b);
+    const double dx = edge - (a ? w.u : w.t), z = dx * (a ? ra : rb);
     double v;
     if (wave_any(!(fabs(z) <= kErfPolyEdge)))
-      v = det_erf(z);
+      v = det_erf_call(dx / (a ? s2a : s2b));
     else
       v = erf_poly(z);
     const double up = __shfl_down(v, 1);
@@ -133,12 +179,14 @@ __device__ __forceinline__ void row_weights(const RowWin& w, int b0, int b1, int
 // (b, 2m + 1) share a Philox block); binomial cells that are not surely 0 wait in LDS until 64
 // of one regime are together, whatever their rows, so a batch fills all lanes.
 template <typename T, int MODE, int TH, int TW>
-__global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>()))
-    k_tile(DepoView<T> d, RasterGeom g, double nsigma, uint64_t seed, T* __restrict__ grid,
-           const int32_t* __restrict__ list, const int32_t* __restrict__ offs, const int32_t* __restrict__ items,
-           const int32_t* __restrict__ item_off, const int32_t* __restrict__ counts, int64_t ntiles,
-           int32_t* __restrict__ ctrl, const DetTables* __restrict__ tables, const double* __restrict__ lf,
-           const int2* __restrict__ hull) {
+__global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(DrawArgs<T> args) {
+  const DepoView<T>& d = args.d;
+  const RasterGeom& g = args.g;
+  const int32_t* __restrict__ list = args.list;
+  const int32_t* __restrict__ counts = args.counts;
+  const int64_t ntiles = args.ntiles;
+  int32_t* __restrict__ ctrl = args.ctrl;
+  T* __restrict__ grid = args.grid;
   constexpr bool BINOM = MODE == kModeBinomial;
   constexpr int NW = 4, WAIT = BINOM ? kWait : 1, UND = BINOM ? kUndecidedBinomial : kUndecidedNormal;
   static_assert(TH * TW <= (1 << kDstBits), "a cell's tag holds its tile offset in kDstBits bits");
@@ -146,13 +194,13 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>()))
   __shared__ uint32_t tile[TH * TW];
   __shared__ float s_a[NW][TH];
   __shared__ alignas(8) float s_b[NW][TW];
-  __shared__ float s_p[NW][WAIT], s_u[NW][WAIT];
-  __shared__ uint32_t s_tag[NW][WAIT], s_und[NW][UND];
+  __shared__ uint32_t s_wait[NW][3 * WAIT];  // probability, uniform, tag
+  __shared__ uint32_t s_und[NW][UND];
   __shared__ float s_n[kRowsPerItem];
   __shared__ float s_sum[NW];
   __shared__ int s_item, s_row;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
+  uint32_t* const wait = s_wait[wv];
   const int zgroup = zero_group(ntiles), nzero = (int)((ntiles + zgroup - 1) / zgroup);
   const int nitems = ctrl[kCtrlNItems];
   bool more_items = true;  // block-uniform
@@ -165,199 +213,202 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>()))
     const bool more_zero = zg < nzero;
     if (!more_items && !more_zero) break;
     __syncthreads();  // every thread has read s_item
-    if (!more_items) {
-      clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
-      continue;
-    }
-    const TileItem w_ = tile_item<TH, TW>(g, item, items, item_off, offs);
-    const int tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
-    const PlaneGeom& pl = g.pl[w_.plane];
-    T* gp = grid + (int64_t)w_.ev * g.grid_ev_stride + pl.grid_off + (int64_t)tb0 * pl.nt + tk0;
-    for (int x = threadIdx.x; x < TH * TW; x += 256) tile[x] = 0;
-    // the rows' electron counts and their sum
-    float n = 0.0f;
-    for (int x = threadIdx.x; x < r1 - r0; x += 256) n += (s_n[x] = electrons_of((double)d.q[list[r0 + x]]));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-    if (lane == 0) s_sum[wv] = n;
-    if (threadIdx.x == 0) s_row = r0;
-    __syncthreads();
-    const bool direct = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) > kTileElectrons;  // block-uniform
-    if (direct && w_.owned) {  // (a split tile is clear already)
-      for (int x = threadIdx.x; x < th * TW; x += 256)
-        if (x % TW < tw) gp[(int64_t)(x / TW) * pl.nt + x % TW] = T(0);
-      __threadfence();
+    if (more_items) {
+      const TileItem w_ = tile_item<TH, TW>(g, item, args.items, args.item_off, args.offs);
+      const int tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
+      const PlaneGeom& pl = g.pl[w_.plane];
+      T* gp = grid + (int64_t)w_.ev * g.grid_ev_stride + pl.grid_off + (int64_t)tb0 * pl.nt + tk0;
+      for (int x = threadIdx.x; x < TH * TW; x += 256) tile[x] = 0;
+      // the rows' electron counts and their sum
+      float n = 0.0f;
+      for (int x = threadIdx.x; x < r1 - r0; x += 256) n += (s_n[x] = electrons_of((double)d.q[list[r0 + x]]));
+  #pragma unroll
+      for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+      if (lane == 0) s_sum[wv] = n;
+      if (threadIdx.x == 0) s_row = r0;
+      __syncthreads();
+      const bool direct = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) > kTileElectrons;  // block-uniform
+      if (direct && w_.owned) {  // (a split tile is clear already)
+        for (int x = threadIdx.x; x < th * TW; x += 256)
+          if (x % TW < tw) gp[(int64_t)(x / TW) * pl.nt + x % TW] = T(0);
+        __threadfence();
+        __syncthreads();
+      }
+      auto add = [&](uint32_t o, int k) {
+        if (k <= 0) return;
+        if (direct)
+          atomicAdd(gp + (int64_t)(o / TW) * pl.nt + o % TW, (T)k);
+        else
+          atomicAdd(&tile[o], (uint32_t)k);
+      };
+      // waiting and undecided cells of this wave (wave-uniform counts)
+      int ni = 0, nc = 0, nx = 0;
+      auto leave = [&](bool undecided, uint32_t tag) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(undecided);
+        if (undecided) s_und[wv][nx + lanes_below(mask)] = tag;
+        nx += __popcll(mask);
+      };
+      // runs whatever holds at least `least` cells, undecided ones first (they are then below
+      // 64 before a batch adds to them)
+      auto run = [&](int least) {
+        for (;;) {
+          if (nx >= least) {
+            const int take = min(nx, 64);
+            nx -= take;
+            wave_sync();
+            if (lane < take) {
+              const uint32_t tag = s_und[wv][nx + lane], o = tag & ((1u << kDstBits) - 1u);
+              const int64_t j = list[r0 + (int)(tag >> kDstBits)];
+              add(o, exact_count<T, MODE>(
+                         (const DrawArgs<T>*)(const void*)__builtin_amdgcn_kernarg_segment_ptr(), j,
+                         tb0 + (int)(o / TW), tk0 + (int)(o % TW)));
+            }
+            wave_sync();
+          } else if (BINOM && ni >= least) {
+            const int take = min(ni, 64);
+            ni -= take;
+            wave_sync();
+            const int at = ni + min(lane, take - 1);
+            const uint32_t tag = wait[2 * WAIT + at];
+            int k;
+            const bool sure =
+                fast_inversion(s_n[tag >> kDstBits], __uint_as_float(wait[at]), __uint_as_float(wait[WAIT + at]), &k);
+            wave_sync();
+            if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
+            leave(lane < take && !sure, tag);
+          } else if (BINOM && nc >= least) {
+            const int take = min(nc, 64);
+            wave_sync();
+            const int at = WAIT - nc + min(lane, take - 1);
+            nc -= take;
+            const uint32_t tag = wait[2 * WAIT + at];
+            int k;
+            const bool sure =
+                fast_chopdown(s_n[tag >> kDstBits], __uint_as_float(wait[at]), __uint_as_float(wait[WAIT + at]), &k);
+            wave_sync();
+            if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
+            leave(lane < take && !sure, tag);
+          } else {
+            break;
+          }
+        }
+      };
+      // the waves claim rows one at a time, so that they finish the item together
+      auto claim = [&]() {
+        int r = 0;
+        if (lane == 0) r = atomicAdd(&s_row, 1);
+        return __builtin_amdgcn_readfirstlane(r);
+      };
+      for (int r = claim(); r < r1; r = claim()) {
+        // the row is wave-uniform: a scalar index makes its parameters scalar loads and registers
+        const int64_t j = __builtin_amdgcn_readfirstlane(list[r]);
+        const RowWin w = row_window(d, j, g, args.nsigma);
+        const int b0 = max(w.b0, tb0), b1 = min(w.b1, tb0 + th);
+        const int k0 = max(w.k0, tk0), k1 = min(w.k1, tk0 + tw);
+        if (!w.ok || b0 >= b1 || k0 >= k1) continue;
+        const float N = electrons_of(w.q);
+        if (!(N > 0.0f)) continue;
+        const uint32_t did = d.depo_id ? (uint32_t)d.depo_id[j] : (uint32_t)j;
+        row_weights(w, b0, b1, k0, k1, N, s_a[wv], s_b[wv], lane);
+        const float* wa = s_a[wv];
+        const float2* wb = reinterpret_cast<const float2*>(s_b[wv]);
+        const float rN = 1.0f / N, zero_limit = fast_zero_limit(N);
+        const uint32_t ev = (uint32_t)w.key_event, pc = (uint32_t)w_.plane << 24;
+        // pairs (bi, pj) of the window, 64 a pass: the position, the Philox counter and the tile
+        // offset advance by 64 pairs without a division
+        const int m0 = k0 >> 1, np = ((k1 - 1) >> 1) - m0 + 1, total = (b1 - b0) * np;
+        const int dq = 64 / np, dr = 64 - dq * np;
+        const uint32_t half_nt = (uint32_t)((pl.nt + 1) >> 1);
+        int bi = lane / np, pj = lane - bi * np;
+        uint32_t ctr = (uint32_t)(b0 + bi) * half_nt + (uint32_t)(m0 + pj);
+        uint32_t dst = (uint32_t)((b0 - tb0 + bi) * TW + 2 * (m0 + pj) - tk0) | ((uint32_t)(r - r0) << kDstBits);
+        const uint32_t ctr_step = (uint32_t)dq * half_nt + (uint32_t)dr, ctr_wrap = half_nt - (uint32_t)np;
+        const uint32_t dst_step = (uint32_t)(dq * TW + 2 * dr), dst_wrap = (uint32_t)(TW - 2 * np);
+        for (int base = 0; base < total; base += 64) {
+          const bool in = base + lane < total;
+          const Philox4 ph = philox_cell(ctr, did, ev, pc, args.key0, args.key1);
+          float a = 0.0f;
+          float2 bw = make_float2(0.0f, 0.0f);
+          if (in) {
+            a = wa[bi];
+            bw = wb[pj];
+          }
+          if constexpr (BINOM) {
+            float mu = a * bw.x, u = (float)ph.w0 * 0x1p-32f;
+            const float mu1 = a * bw.y, u1 = (float)ph.w2 * 0x1p-32f;
+            uint32_t tag = dst;
+  #pragma unroll 1
+            for (int half = 0; half < 2; ++half) {
+              const bool need = in && !(u + mu < zero_limit);
+              const bool top = need && mu >= (float)kMuSwitch;
+              const uint64_t mall = __builtin_amdgcn_ballot_w64(need), mtop = __builtin_amdgcn_ballot_w64(top);
+              const uint64_t mlow = mall & ~mtop;
+              if (mall) {
+                const int low = ni + lanes_below(mlow), high = WAIT - 1 - nc - lanes_below(mtop);
+                const int at = top ? high : low;
+                if (need) {
+                  wait[at] = __float_as_uint(mu * rN);
+                  wait[WAIT + at] = __float_as_uint(u);
+                  wait[2 * WAIT + at] = tag;
+                }
+                ni += __popcll(mlow);
+                nc += __popcll(mtop);
+                run(64);
+              }
+              mu = mu1;
+              u = u1;
+              tag = dst + 1;
+            }
+          } else {
+            float ze, zo;
+            const bool ok = fast_normal_pair(ph.w0, ph.w1, ph.w2, &ze, &zo);
+            const float mue = a * bw.x, muo = a * bw.y;
+            int ke, ko;
+            const bool se = fast_normal_count(N, mue, mue * rN, ze, &ke) && ok;
+            const bool so = fast_normal_count(N, muo, muo * rN, zo, &ko) && ok;
+            if (in && se) add(dst & ((1u << kDstBits) - 1u), ke);
+            if (in && so) add((dst & ((1u << kDstBits) - 1u)) + 1, ko);
+            leave(in && !se, dst);
+            leave(in && !so, dst + 1);
+            run(64);
+          }
+          const bool wrap = pj + dr >= np;
+          pj += wrap ? dr - np : dr;
+          bi += wrap ? dq + 1 : dq;
+          ctr += wrap ? ctr_step + ctr_wrap : ctr_step;
+          dst += wrap ? dst_step + dst_wrap : dst_step;
+        }
+      }
+      run(1);
+      __syncthreads();
+      if (!direct) {
+        constexpr int V = 16 / (int)sizeof(T);
+        if (w_.owned && tw == TW && pl.nt % V == 0 && (reinterpret_cast<uintptr_t>(gp) & 15) == 0) {
+          constexpr int VR = TW / V;  // 16-byte vectors per tile row
+          for (int x = threadIdx.x; x < th * VR; x += 256) {
+            const int rr = x / VR, c = x - (x / VR) * VR;
+            const uint32_t* src = &tile[rr * TW + c * V];
+            T v[V];
+  #pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = (T)src[e];
+            *reinterpret_cast<float4*>(gp + (int64_t)rr * pl.nt + c * V) = *reinterpret_cast<const float4*>(v);
+          }
+        } else {
+          for (int x = threadIdx.x; x < th * TW; x += 256) {
+            const int rr = x / TW, c = x - (x / TW) * TW;
+            if (c < tw) {
+              T* dst = gp + (int64_t)rr * pl.nt + c;
+              if (w_.owned)
+                *dst = (T)tile[x];
+              else if (tile[x] != 0)
+                atomicAdd(dst, (T)tile[x]);
+            }
+          }
+        }
+      }
       __syncthreads();
     }
-    auto add = [&](uint32_t o, int k) {
-      if (k <= 0) return;
-      if (direct)
-        atomicAdd(gp + (int64_t)(o / TW) * pl.nt + o % TW, (T)k);
-      else
-        atomicAdd(&tile[o], (uint32_t)k);
-    };
-    // waiting and undecided cells of this wave (wave-uniform counts)
-    int ni = 0, nc = 0, nx = 0;
-    auto leave = [&](bool undecided, uint32_t tag) {
-      const uint64_t mask = __ballot(undecided);
-      if (undecided) s_und[wv][nx + lanes_below(mask)] = tag;
-      nx += __popcll(mask);
-    };
-    // runs whatever holds at least `least` cells, undecided ones first (they are then below
-    // 64 before a batch adds to them)
-    auto run = [&](int least) {
-      for (;;) {
-        if (nx >= least) {
-          const int take = min(nx, 64);
-          nx -= take;
-          wave_sync();
-          if (lane < take) {
-            const uint32_t tag = s_und[wv][nx + lane], o = tag & ((1u << kDstBits) - 1u);
-            const int64_t j = list[r0 + (int)(tag >> kDstBits)];
-            add(o, exact_count<T, MODE>(d, g, nsigma, key0, key1, j, tb0 + (int)(o / TW), tk0 + (int)(o % TW), *tables,
-                                        lf));
-          }
-          wave_sync();
-        } else if (BINOM && ni >= least) {
-          const int take = min(ni, 64);
-          ni -= take;
-          wave_sync();
-          const int at = ni + min(lane, take - 1);
-          const uint32_t tag = s_tag[wv][at];
-          int k;
-          const bool sure = fast_inversion(s_n[tag >> kDstBits], s_p[wv][at], s_u[wv][at], &k);
-          wave_sync();
-          if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
-          leave(lane < take && !sure, tag);
-        } else if (BINOM && nc >= least) {
-          const int take = min(nc, 64);
-          wave_sync();
-          const int at = kWait - nc + min(lane, take - 1);
-          nc -= take;
-          const uint32_t tag = s_tag[wv][at];
-          int k;
-          const bool sure = fast_chopdown(s_n[tag >> kDstBits], s_p[wv][at], s_u[wv][at], &k);
-          wave_sync();
-          if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
-          leave(lane < take && !sure, tag);
-        } else {
-          break;
-        }
-      }
-    };
-    // the waves claim rows one at a time, so that they finish the item together
-    auto claim = [&]() {
-      int r = 0;
-      if (lane == 0) r = atomicAdd(&s_row, 1);
-      return __builtin_amdgcn_readfirstlane(r);
-    };
-    for (int r = claim(); r < r1; r = claim()) {
-      // the row is wave-uniform: a scalar index makes its parameters scalar loads and registers
-      const int64_t j = __builtin_amdgcn_readfirstlane(list[r]);
-      const RowWin w = row_window(d, j, g, nsigma);
-      const int b0 = max(w.b0, tb0), b1 = min(w.b1, tb0 + th);
-      const int k0 = max(w.k0, tk0), k1 = min(w.k1, tk0 + tw);
-      if (!w.ok || b0 >= b1 || k0 >= k1) continue;
-      const float N = electrons_of(w.q);
-      if (!(N > 0.0f)) continue;
-      const uint32_t did = d.depo_id ? (uint32_t)d.depo_id[j] : (uint32_t)j;
-      row_weights(w, b0, b1, k0, k1, N, s_a[wv], s_b[wv], lane);
-      const float* wa = s_a[wv];
-      const float2* wb = reinterpret_cast<const float2*>(s_b[wv]);
-      const float rN = 1.0f / N, zero_limit = fast_zero_limit(N);
-      const uint32_t ev = (uint32_t)w.key_event, pc = (uint32_t)w_.plane << 24;
-      // pairs (bi, pj) of the window, 64 a pass: the position, the Philox counter and the tile
-      // offset advance by 64 pairs without a division
-      const int m0 = k0 >> 1, np = ((k1 - 1) >> 1) - m0 + 1, total = (b1 - b0) * np;
-      const int dq = 64 / np, dr = 64 - dq * np;
-      const uint32_t half_nt = (uint32_t)((pl.nt + 1) >> 1);
-      int bi = lane / np, pj = lane - bi * np;
-      uint32_t ctr = (uint32_t)(b0 + bi) * half_nt + (uint32_t)(m0 + pj);
-      uint32_t dst = (uint32_t)((b0 - tb0 + bi) * TW + 2 * (m0 + pj) - tk0) | ((uint32_t)(r - r0) << kDstBits);
-      const uint32_t ctr_step = (uint32_t)dq * half_nt + (uint32_t)dr, ctr_wrap = half_nt - (uint32_t)np;
-      const uint32_t dst_step = (uint32_t)(dq * TW + 2 * dr), dst_wrap = (uint32_t)(TW - 2 * np);
-      for (int base = 0; base < total; base += 64) {
-        const bool in = base + lane < total;
-        const Philox4 ph = philox4x32_10(ctr, did, ev, pc, key0, key1);
-        float a = 0.0f;
-        float2 bw = make_float2(0.0f, 0.0f);
-        if (in) {
-          a = wa[bi];
-          bw = wb[pj];
-        }
-        if constexpr (BINOM) {
-          float mu = a * bw.x, u = (float)ph.w0 * 0x1p-32f;
-          const float mu1 = a * bw.y, u1 = (float)ph.w2 * 0x1p-32f;
-          uint32_t tag = dst;
-#pragma unroll 1
-          for (int half = 0; half < 2; ++half) {
-            const bool need = in && !(u + mu < zero_limit);
-            const bool top = need && mu >= (float)kMuSwitch;
-            const uint64_t mtop = __ballot(top), mall = __ballot(need), mlow = mall & ~mtop;
-            if (mall) {
-              const int at = top ? kWait - 1 - nc - lanes_below(mtop) : ni + lanes_below(mlow);
-              if (need) {
-                s_p[wv][at] = mu * rN;
-                s_u[wv][at] = u;
-                s_tag[wv][at] = tag;
-              }
-              ni += __popcll(mlow);
-              nc += __popcll(mtop);
-              run(64);
-            }
-            mu = mu1;
-            u = u1;
-            tag = dst + 1;
-          }
-        } else {
-          float ze, zo;
-          const bool ok = fast_normal_pair(ph.w0, ph.w1, ph.w2, &ze, &zo);
-          const float mue = a * bw.x, muo = a * bw.y;
-          int ke, ko;
-          const bool se = fast_normal_count(N, mue, mue * rN, ze, &ke) && ok;
-          const bool so = fast_normal_count(N, muo, muo * rN, zo, &ko) && ok;
-          if (in && se) add(dst & ((1u << kDstBits) - 1u), ke);
-          if (in && so) add((dst & ((1u << kDstBits) - 1u)) + 1, ko);
-          leave(in && !se, dst);
-          leave(in && !so, dst + 1);
-          run(64);
-        }
-        const bool wrap = pj + dr >= np;
-        pj += wrap ? dr - np : dr;
-        bi += wrap ? dq + 1 : dq;
-        ctr += wrap ? ctr_step + ctr_wrap : ctr_step;
-        dst += wrap ? dst_step + dst_wrap : dst_step;
-      }
-    }
-    run(1);
-    __syncthreads();
-    if (!direct) {
-      constexpr int V = 16 / (int)sizeof(T);
-      if (w_.owned && tw == TW && pl.nt % V == 0 && (reinterpret_cast<uintptr_t>(gp) & 15) == 0) {
-        constexpr int VR = TW / V;  // 16-byte vectors per tile row
-        for (int x = threadIdx.x; x < th * VR; x += 256) {
-          const int rr = x / VR, c = x - (x / VR) * VR;
-          const uint32_t* src = &tile[rr * TW + c * V];
-          T v[V];
-#pragma unroll
-          for (int e = 0; e < V; ++e) v[e] = (T)src[e];
-          *reinterpret_cast<float4*>(gp + (int64_t)rr * pl.nt + c * V) = *reinterpret_cast<const float4*>(v);
-        }
-      } else {
-        for (int x = threadIdx.x; x < th * TW; x += 256) {
-          const int rr = x / TW, c = x - (x / TW) * TW;
-          if (c < tw) {
-            T* dst = gp + (int64_t)rr * pl.nt + c;
-            if (w_.owned)
-              *dst = (T)tile[x];
-            else if (tile[x] != 0)
-              atomicAdd(dst, (T)tile[x]);
-          }
-        }
-      }
-    }
-    __syncthreads();
-    if (more_zero) clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, hull, grid);
+    if (more_zero) clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, args.hull, grid);
   }
 }
 
@@ -365,10 +416,25 @@ template <typename T, int TH, int TW>
 hipError_t launch_tile_draw(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed, T* grid,
                             const RasterWs& ws, const DetTables* tables, const double* lfact, int n_cu,
                             hipStream_t st) {
-#define WCT_DRAW_LAUNCH(M)                                                                                        \
-  hipLaunchKernelGGL((k_tile<T, M, TH, TW>), dim3((unsigned)(n_cu * draw_blocks<M, TH, TW>())), dim3(256), 0, st, d, g, \
-                     nsigma, seed, grid, ws.list, ws.offs, ws.items, ws.item_off, ws.counts, ws.ntiles, ws.ctrl,  \
-                     tables, lfact, ws.hull)
+  DrawArgs<T> a{};
+  a.d = d;
+  a.g = g;
+  a.nsigma = nsigma;
+  a.key0 = (uint32_t)seed;
+  a.key1 = (uint32_t)(seed >> 32);
+  a.grid = grid;
+  a.list = ws.list;
+  a.offs = ws.offs;
+  a.items = ws.items;
+  a.item_off = ws.item_off;
+  a.counts = ws.counts;
+  a.ntiles = ws.ntiles;
+  a.ctrl = ws.ctrl;
+  a.tables = tables;
+  a.lf = lfact;
+  a.hull = ws.hull;
+#define WCT_DRAW_LAUNCH(M) \
+  hipLaunchKernelGGL((k_tile<T, M, TH, TW>), dim3((unsigned)(n_cu * draw_blocks<M, TH, TW>())), dim3(256), 0, st, a)
   if (mode == kModeBinomial)
     WCT_DRAW_LAUNCH(kModeBinomial);
   else
