@@ -275,14 +275,14 @@ RasterWs carve_raster(const wct_plan* P, Carver& cv, int n_events, int64_t n_row
   RasterWs w;
   w.ntiles = (int64_t)n_events * P->ntiles_ev;
   const int64_t nrow = n_rows > 0 ? n_rows : 1;
-  w.max_items = w.ntiles + (4 * nrow + kRowsPerItem - 1) / kRowsPerItem + 1;
   const int64_t nsb = (w.ntiles + kScanPerBlock - 1) / kScanPerBlock;
   w.ctrl = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (kCtrlWords + w.ntiles)));
   w.counts = w.ctrl ? w.ctrl + kCtrlWords : nullptr;
-  w.rank = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
+  // the items (at most ntiles + 4 n / 2^kItemShiftMin) are written once the slots are used
+  w.rank = w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
+  cv.take(sizeof(int32_t) * (w.ntiles + (4 * nrow + 255) / 256 + 1));
   w.offs = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
   w.item_off = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
-  w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * w.max_items));
   w.list = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
   w.big = static_cast<int32_t*>(cv.take(sizeof(int32_t) * nrow));
   w.blocks = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 2 * (nsb > 0 ? nsb : 1)));

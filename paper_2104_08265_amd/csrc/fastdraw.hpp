@@ -15,10 +15,12 @@
 //    in the last place); the sums weigh the k-th step's error by pmf(k): 6 e E[k] <= 60 e
 //    for the inversion, 6 e 0.8 sqrt(N p) for the search from the mode;
 //  * one rounding per subtraction from u: below e / 2 each, at most 30 that matter;
-//  * u: 26 of its 53 bits and one rounding: e.
-// Together below 190 e = 1.2e-5 for the inversion and 30 e + 8 e sqrt(N p) for the mode
-// search; the margins are 6e-5 and 6e-5 + 1.5e-6 sqrt(N p), five and three times that.
-// Random inputs leave 0.1 to 0.4% of the cells undecided.
+//  * u: 19 of its 53 bits and half a unit of the last: 16 e;
+//  * p rounded to 17 bits of mantissa: 64 e relative, which moves a sum by at most
+//    26 e sqrt(N p).
+// Together below 206 e + 26 e sqrt(N p) = 1.8e-5 for the inversion and 50 e + 34 e sqrt(N p)
+// for the mode search; the margins are 2.5e-5 and 2.5e-5 + 4e-6 sqrt(N p).
+// Random inputs leave 0.05 to 0.2% of the cells undecided.
 #pragma once
 
 #include <cmath>
@@ -56,9 +58,10 @@ WCT_HD float fast_sqrt(float x) {
 #endif
 }
 
-constexpr float kDrawMargin = 6e-5f;        // what the sums must keep from u
-constexpr float kDrawMarginSigma = 1.5e-6f; // times sqrt(N p), for the search from the mode
-constexpr int kFastSteps = 126;             // inversion steps at most (even)
+constexpr float kDrawMargin = 2.5e-5f;       // what the sums must keep from u
+constexpr float kDrawMarginSigma = 4e-6f; // times sqrt(N p), for the search from the mode
+constexpr int kFastSteps = 126;             // inversion steps at most
+constexpr int kFastUnrolled = 21;           // the first that is not unrolled (odd)
 constexpr int kFastPasses = 512;            // passes of the search from the mode at most
 constexpr float kFastMaxMean = 4096.0f;     // means up to which 512 passes hold eight widths
 constexpr float kFastMaxN = 67108864.0f;    // 2^26: above it the FP64 ln(n!) itself is only good to 1e-6
@@ -68,20 +71,60 @@ constexpr float kFastMaxN = 67108864.0f;    // 2^26: above it the FP64 ln(n!) it
 // then N p >= 3/2 for three electrons or more, so only rows of one or two are kept out.
 WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : 1.0f - 1e-5f; }
 
-struct FastInv {
-  float v[kFastSteps + 2];
-};
-constexpr FastInv make_fast_inv() {
-  FastInv t{};
-  for (int j = 1; j < kFastSteps + 2; ++j) t.v[j] = 1.0f / (float)j;
-  return t;
+// A cell that waits for its batch, in 64 bits.  x: the probability, below 1/2 where it can be
+// decided (so its upper two bits are 0), to 17 bits of mantissa, over the row's index in the
+// work item; y: 19 bits of the uniform over the cell's offset in the tile.
+constexpr uint32_t kEntryRow = 255u;
+constexpr int kEntryDstBits = 13;
+constexpr uint32_t kEntryDst = (1u << kEntryDstBits) - 1u;
+WCT_HD uint32_t float_bits(float v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __float_as_uint(v);
+#else
+  return __builtin_bit_cast(uint32_t, v);
+#endif
 }
-constexpr FastInv kInvF = make_fast_inv();
+WCT_HD float bits_float(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __uint_as_float(v);
+#else
+  return __builtin_bit_cast(float, v);
+#endif
+}
+WCT_HD uint32_t entry_x(float p, uint32_t row) { return (((float_bits(p) + 32u) << 2) & ~kEntryRow) | row; }
+WCT_HD uint32_t entry_y(uint32_t w, uint32_t dst) { return (w & ~kEntryDst) | dst; }
+WCT_HD float entry_p(uint32_t x) { return bits_float((x & ~kEntryRow) >> 2); }
+WCT_HD float entry_u(uint32_t y) { return (float)((y & ~kEntryDst) | (1u << (kEntryDstBits - 1))) * 0x1p-32f; }
+
+// The inversion's steps: f(k + 1) = f(k) (c1 / (k + 1) + nr), with v = u - F(k) and its
+// smallest modulus so far.
+struct FastSearch {
+  float f, v, near, c1, nr;
+  int k;
+  WCT_HD void step(float inv) {
+    f *= fmaf(c1, inv, nr);
+    v -= f;
+    near = fminf(near, fabsf(v));
+    k += v >= 0.0f ? 1 : 0;
+  }
+};
+// The first steps with 1 / (k + 1) in the code, two between tests (a table of them costs a
+// scalar load's latency every pass).
+template <int J>
+WCT_HD void fast_steps(FastSearch& t) {
+  if constexpr (J < kFastUnrolled) {
+    if (any_lane(t.v >= kDrawMargin)) {
+      t.step(1.0f / (float)J);
+      t.step(1.0f / (float)(J + 1));
+      fast_steps<J + 2>(t);
+    }
+  }
+}
 
 // Inversion from 0 (N p < 10).  The lanes of a wave step together until none searches.
 WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
   const float mu = N * p;
-  const bool fits = (mu < kMuSwitch - 1e-4f) & (p < 0.4999f);
+  const bool fits = (mu < (float)kMuSwitch - 1e-4f) & (p < 0.4999f);
   // -ln(1 - p) = 2 atanh(p / (2 - p))
   const float s = p * fast_rcp(2.0f - p), s2 = s * s;
   float poly = 1.0f / 13.0f;
@@ -94,22 +137,15 @@ WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
   float f = fast_exp2((N * s) * poly * (float)(-2.0 * kLog2e));
   // f(k+1) = f(k) (r (N - k)) / (k + 1) = f(k) (r (N + 1) / (k + 1) - r)
   const float r = p * fast_rcp(1.0f - p), c1 = fmaf(r, N, r);
-  float v = fits ? u - f : -1.0f;  // u - F(0); undecided cells do not search
-  float near = fabsf(v);
-  int k = v >= 0.0f ? 1 : 0;
-  for (int j = 1; j < kFastSteps; j += 2) {
-    if (!any_lane(v >= kDrawMargin)) break;
-    f *= fmaf(c1, kInvF.v[j], -r);
-    v -= f;
-    near = fminf(near, fabsf(v));
-    k += v >= 0.0f ? 1 : 0;
-    f *= fmaf(c1, kInvF.v[j + 1], -r);
-    v -= f;
-    near = fminf(near, fabsf(v));
-    k += v >= 0.0f ? 1 : 0;
+  const float v = fits ? u - f : -1.0f;  // u - F(0); undecided cells do not search
+  FastSearch t{f, v, fabsf(v), c1, -r, v >= 0.0f ? 1 : 0};
+  fast_steps<1>(t);
+  for (int j = kFastUnrolled; j <= kFastSteps; ++j) {  // few waves come here
+    if (!any_lane(t.v >= kDrawMargin)) break;
+    t.step(fast_rcp((float)j));
   }
-  *count = k;
-  return fits & (near >= kDrawMargin) & (v < 0.0f);
+  *count = t.k;
+  return fits & (t.near >= kDrawMargin) & (t.v < 0.0f);
 }
 
 // (1 + e) ln(1 + e) - e over e^2, |e| <= 0.1
@@ -134,8 +170,8 @@ WCT_HD float fast_stirling(float rn) {
 WCT_HD bool fast_chopdown(float N, float p, float u, int* count) {
   const float a = fmaf(N, p, p);  // (N + 1) p
   const float m = floorf(a), fr = a - m, mu = a - p;
-  const float tol = 8e-7f * a;
-  const bool fits = (fr > tol) & (fr < 1.0f - tol) & (p < 0.4999f) & (mu > kMuSwitch + 1e-4f) & (mu < kFastMaxMean) &
+  const float tol = 6e-6f * a;  // p's error (68 e relative) decides the mode's floor
+  const bool fits = (fr > tol) & (fr < 1.0f - tol) & (p < 0.4999f) & (mu > (float)kMuSwitch + 1e-4f) & (mu < kFastMaxMean) &
                     (N < kFastMaxN);
   const float nm = N - m, nq = N - mu, q = 1.0f - p, x = p - fr;
   const float rN = fast_rcp(N), rm = fast_rcp(m), rnm = fast_rcp(nm);

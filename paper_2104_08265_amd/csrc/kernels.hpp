@@ -36,7 +36,8 @@ enum RasterCtrl {
   kCtrlWords = 64 + 8 * 32
 };
 constexpr int kQueues = 8, kQueueStride = 32;  // one queue per XCD, each head on its own 128-byte line
-constexpr int kRowsPerItem = 256;  // rows one tile work item processes at most
+// Rows one tile work item processes at most: 2^shift, chosen per call (item_shift).
+constexpr int kItemShiftMin = 4, kItemShiftMax = 8;
 constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kernels at most
 constexpr int kScanPerBlock = 4096;
 
@@ -72,15 +73,15 @@ inline const TileVariantDesc* tile_variants(int* count) {
 struct RasterWs {
   int32_t* ctrl;      // kCtrlWords
   int32_t* counts;    // [ntiles]
-  int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches
+  int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches (until k_fill)
   int32_t* offs;      // [ntiles + 1]
   int32_t* item_off;  // [ntiles + 1]
-  int32_t* items;     // [max_items]
+  int32_t* items;     // over rank and the room behind it: at least 4 n + ntiles
   int32_t* list;      // [4 n]
   int32_t* big;       // [n]
   int32_t* blocks;    // [2 * nscan_blocks]
   int64_t ntiles;
-  int64_t max_items;
+  int item_shift;
   int2* span = nullptr;  // optional [event][rows_ev] tick spans of the rows (row_span)
   int2* hull = nullptr;  // with span: [event][bands] tile-column hull of each band of TH rows
 };

@@ -8,7 +8,7 @@
 //                  and keeps the value each increment returns, its slot in that tile's
 //                  row list; optionally it marks the impact rows its window reaches;
 //  2. scan       - exclusive prefix sums give each tile its slice of a row list and
-//                  a number of work items (ceil(rows / kRowsPerItem); 0 for an empty tile);
+//                  a number of work items (of up to 2^item_shift rows; 0 for an empty tile);
 //  3. k_fill     - rows are written into their tiles' slices at their slots (plain stores);
 //  4. the tile kernel (rastermean.hip for the mean, rasterdraw.hip for drawn counts) - persistent
 //                  blocks take work items from striped queues (next_item) and, in step, groups
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(256) k_band_spans(RasterGeom g, const int32_t*
 
 // 2. scan of (rows, items) per tile -------------------------------------------
 // Tiles no row touches get no work item: the tile kernel clears them in groups.
-__device__ __forceinline__ int items_of(int c) { return (c + kRowsPerItem - 1) / kRowsPerItem; }
+__device__ __forceinline__ int items_of(int c, int shift) { return (c + (1 << shift) - 1) >> shift; }
 
 // Inclusive block scan of int2 over 1024 threads (16 waves of 64).
 __device__ int2 block_scan_incl(int2 v, int2* s_wave) {
@@ -413,7 +413,7 @@ __device__ int2 block_scan_incl(int2 v, int2* s_wave) {
   return v;
 }
 
-__global__ void __launch_bounds__(1024) k_scan_local(const int32_t* __restrict__ counts, int64_t n,
+__global__ void __launch_bounds__(1024) k_scan_local(const int32_t* __restrict__ counts, int64_t n, int shift,
                                                      int2* __restrict__ blocks) {
   __shared__ int2 s_wave[16];
   const int64_t base = (int64_t)blockIdx.x * kScanPerBlock + threadIdx.x * 4;
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(1024) k_scan_local(const int32_t* __restrict__
     if (base + e < n) {
       const int c = counts[base + e];
       s.x += c;
-      s.y += items_of(c);
+      s.y += items_of(c, shift);
     }
   const int2 incl = block_scan_incl(s, s_wave);
   if (threadIdx.x == blockDim.x - 1) blocks[blockIdx.x] = incl;
@@ -450,7 +450,7 @@ __global__ void __launch_bounds__(1024) k_scan_blocks(int2* __restrict__ blocks,
   }
 }
 
-__global__ void __launch_bounds__(1024) k_scan_apply(const int32_t* __restrict__ counts, int64_t n,
+__global__ void __launch_bounds__(1024) k_scan_apply(const int32_t* __restrict__ counts, int64_t n, int shift,
                                                      const int2* __restrict__ blocks, int32_t* __restrict__ offs,
                                                      int32_t* __restrict__ item_off) {
   __shared__ int2 s_wave[16];
@@ -460,7 +460,7 @@ __global__ void __launch_bounds__(1024) k_scan_apply(const int32_t* __restrict__
   for (int e = 0; e < 4; ++e) {
     c[e] = base + e < n ? counts[base + e] : 0;
     s.x += c[e];
-    s.y += base + e < n ? items_of(c[e]) : 0;
+    s.y += base + e < n ? items_of(c[e], shift) : 0;
   }
   const int2 incl = block_scan_incl(s, s_wave);
   const int2 bo = blocks[blockIdx.x];
@@ -471,7 +471,7 @@ __global__ void __launch_bounds__(1024) k_scan_apply(const int32_t* __restrict__
       offs[t] = run.x;
       item_off[t] = run.y;
       run.x += c[e];
-      run.y += items_of(c[e]);
+      run.y += items_of(c[e], shift);
       if (t == n - 1) {
         offs[n] = run.x;
         item_off[n] = run.y;
@@ -508,9 +508,10 @@ __global__ void k_items(const int32_t* __restrict__ item_off, int64_t ntiles, in
 
 // Tiles that several work items accumulate into start from zero.
 template <typename T, int TH, int TW>
-__global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, int64_t ntiles, T* __restrict__ grid) {
+__global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, int64_t ntiles, int shift,
+                             T* __restrict__ grid) {
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x)
-    if (counts[t] > kRowsPerItem) zero_tile<T, TH, TW>(g, t, grid);
+    if (counts[t] > (1 << shift)) zero_tile<T, TH, TW>(g, t, grid);
 }
 
 // 5. rows wider than 4 tiles: 64 x 64 chunks per wave, straight to global atomics ------
@@ -568,12 +569,25 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
     if (e_ != hipSuccess) return e_;        \
   } while (0)
 
+// Rows per work item.  An item's time grows with its rows, and the call ends with its last
+// block: of items of 256 rows the track event (3e5 rows, 6.5e5 row visits of tiles) has
+// 7220 for 1024 blocks and would end 1.47 times later than with the work dealt out evenly
+// (items of 64 rows 1.22), an event of 6000 rows on one track 95 items, 23 times (16 rows:
+// 2.5).  Smaller items cost more tile writes by atomics.  So: about the rows a CU has in
+// 1/64 of the call, between 16 and 256.
+static int item_shift(int64_t n, int mode, int n_cu) {
+  int s = kItemShiftMin;
+  while (s < kItemShiftMax && ((int64_t)(mode == kModeMean ? 8 : 64) * n_cu << s) < n) ++s;
+  return s;
+}
+
 template <typename T, int TH, int TW>
 hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed,
-                               T* grid, const RasterWs& ws, const DetTables* tables, const double* lfact, int n_cu,
+                               T* grid, RasterWs ws, const DetTables* tables, const double* lfact, int n_cu,
                                hipStream_t st, ProfHook* prof) {
   const int64_t nt = ws.ntiles;
   if (nt >= INT32_MAX) return hipErrorInvalidValue;  // tile indices and list offsets are int32
+  ws.item_shift = item_shift(d.n, mode, n_cu);
   if (prof) prof->begin("raster_bin", st);
   // control words and counts are contiguous
   hipError_t e = launch_fill_i32(ws.ctrl, kCtrlWords + nt, 0, st);
@@ -600,11 +614,11 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
   }
   const int nsb = (int)((nt + kScanPerBlock - 1) / kScanPerBlock);
   int2* blocks = reinterpret_cast<int2*>(ws.blocks);
-  hipLaunchKernelGGL(k_scan_local, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, blocks);
+  hipLaunchKernelGGL(k_scan_local, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, ws.item_shift, blocks);
   WCT_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, blocks, nsb, ws.ctrl);
   WCT_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, blocks, ws.offs, ws.item_off);
+  hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, ws.item_shift, blocks, ws.offs, ws.item_off);
   WCT_CHECK_LAUNCH();
   if (d.n > 0) {
     hipLaunchKernelGGL((k_fill<T, TH, TW>), dim3(rblocks), dim3(256), 0, st, d, g, nsigma, ws.offs, ws.rank,
@@ -613,7 +627,8 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
   }
   hipLaunchKernelGGL(k_items, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, ws.item_off, nt, ws.items);
   WCT_CHECK_LAUNCH();
-  hipLaunchKernelGGL((k_zero_split<T, TH, TW>), dim3(1024), dim3(256), 0, st, g, ws.counts, nt, grid);
+  hipLaunchKernelGGL((k_zero_split<T, TH, TW>), dim3(1024), dim3(256), 0, st, g, ws.counts, nt, ws.item_shift,
+                     grid);
   WCT_CHECK_LAUNCH();
   if (prof) prof->end(st);
   static const char* const kTileName[3] = {"raster_tile_mean", "raster_tile_fluct", "raster_tile_normal"};

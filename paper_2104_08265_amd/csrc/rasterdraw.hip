@@ -10,7 +10,7 @@
 // where 32-bit integer ones take 5.4 (measured, 256-thread blocks, any address pattern).  A
 // tile is therefore summed in 32-bit integers and converted when it is written; an item
 // whose electrons could overflow them adds to the grid directly.  Together: three-plane
-// event of 1e5 depositions 6.3 -> 3.6 ms, two-face showers of 1e6 depositions 37 -> 21 ms.
+// event of 1e5 depositions 6.3 -> 2.7 ms, two-face showers of 1e6 depositions 37 -> 20 ms.
 #include "erfpoly.hpp"
 #include "fastdraw.hpp"
 #include "rasterwin.hpp"
@@ -19,21 +19,25 @@ namespace wct {
 
 namespace {
 
-constexpr int kDstBits = 13;  // a cell's offset in its tile; above it, the row's index in the item
-static_assert(kRowsPerItem <= 256, "a cell's tag holds the row's index in 8 bits");
+constexpr int kItemRows = 1 << kItemShiftMax;
+static_assert(kItemRows - 1 <= (int)kEntryRow, "an entry holds the row's index in the item");
 // Cells waiting for a batch of 64, per wave: inversion entries from the bottom, mode-search
-// entries from the top (each below 64 before a push of at most 64 cells in all).
-constexpr int kWait = 192;
+// entries from the top (each below 64 before a tick pair's push of at most 128 in all).
+constexpr int kWait = 256;
 // Cells left undecided: below 64 before a batch adds 64 (binomial) or a tick pair 128 (normal).
+// They are kept across items (undecided_entry).
 constexpr int kUndecidedBinomial = 128, kUndecidedNormal = 192;
 // Electrons of an item up to which its 32-bit tile cannot overflow (the sum is rounded).
 constexpr float kTileElectrons = 4.0e9f;
 
-// Blocks per CU: what LDS holds (160 KB), at most four (128 vector registers).
+// Waves per block (they share a tile), and blocks per CU: what LDS holds (160 KB), at most
+// four (128 vector registers; five waves per SIMD or more spill: 7.6 to 9.4 ms for the
+// event that took 6.6).
+constexpr int kDrawWaves = 4, kDrawThreads = 64 * kDrawWaves;
 template <int MODE, int TH, int TW>
 constexpr int draw_blocks() {
-  constexpr int lds = 4 * TH * TW + 16 * (TH + TW) + 4 * kRowsPerItem +
-                      (MODE == kModeBinomial ? 16 * kUndecidedBinomial + 48 * kWait : 16 * kUndecidedNormal) + 128;
+  constexpr int wave = 4 * (TH + TW) + (MODE == kModeBinomial ? 8 * kUndecidedBinomial + 8 * kWait : 8 * kUndecidedNormal);
+  constexpr int lds = 4 * TH * TW + 4 * kItemRows + kDrawWaves * wave + 128;
   constexpr int n = 163840 / lds;
   return n > 4 ? 4 : n;
 }
@@ -59,6 +63,7 @@ struct DrawArgs {
   T* grid;
   const int32_t *list, *offs, *items, *item_off, *counts;
   int64_t ntiles;
+  int item_shift;
   int32_t* ctrl;
   const DetTables* tables;
   const double* lf;
@@ -90,17 +95,34 @@ __device__ __forceinline__ Philox4 philox_cell(uint32_t c0, uint32_t c1, uint32_
 
 __device__ __forceinline__ float electrons_of(double q) { return (float)floor(fmin(q + 0.5, 2147483647.0)); }
 
-// The defining computation of one cell's count (lanes may hold cells of different rows).
+// An undecided cell: the row, and the cell's offset in its tile below the tile's row and
+// column modulo 8 (a row of the tile path reaches at most four tiles).
+__device__ __forceinline__ uint32_t undecided_tile(int tr, int tc) {
+  return ((uint32_t)tr & 7u) << kEntryDstBits | ((uint32_t)tc & 7u) << (kEntryDstBits + 3);
+}
+
+// The defining computation of one cell's count (lanes may hold cells of different rows); the
+// cell's index in the grid goes to *at.
 // Out of line, like the erf series: inlined, the FP64 constants of both cost the loop over
 // cells about 470 spilled scalar registers.
-template <typename T, int MODE>
-__device__ __attribute__((noinline)) int exact_count(const DrawArgs<T>* args, int64_t j, int b, int k) {
+template <typename T, int MODE, int TH, int TW>
+__device__ __attribute__((noinline)) int exact_count(const DrawArgs<T>* args, uint2 cell, int64_t* at) {
   const DepoView<T>& d = args->d;
   const RasterGeom& g = args->g;
   const DetTables& tb = *args->tables;
   const double* __restrict__ lf = args->lf;
+  const int64_t j = cell.x;
   const RowWin w = row_window(d, j, g, args->nsigma);
-  if (!w.ok || b < w.b0 || b >= w.b1 || k < w.k0 || k >= w.k1) return 0;
+  const int off = (int)(cell.y & kEntryDst), tr0 = w.b0 / TH, tc0 = w.k0 / TW;
+  const int tr = tr0 + (((int)(cell.y >> kEntryDstBits) - tr0) & 7);
+  const int tc = tc0 + (((int)(cell.y >> (kEntryDstBits + 3)) - tc0) & 7);
+  const int b = tr * TH + off / TW, k = tc * TW + off % TW;
+  if (!w.ok || b < w.b0 || b >= w.b1 || k < w.k0 || k >= w.k1) {  // the tick beside a window's end
+    *at = 0;
+    return 0;
+  }
+  const PlaneGeom& pl = g.pl[w.plane];
+  *at = (int64_t)w.event * g.grid_ev_stride + pl.grid_off + (int64_t)b * pl.nt + k;
   const double s2a = w.su * kSqrt2, s2b = w.st * kSqrt2;
   double e[4];
 #pragma unroll 1
@@ -116,7 +138,7 @@ __device__ __attribute__((noinline)) int exact_count(const DrawArgs<T>* args, in
   const double p = (0.5 * (e[1] - e[0])) * (0.5 * (e[3] - e[2]));
   const int N = (int)floor(fmin(w.q + 0.5, 2147483647.0));
   const uint32_t did = d.depo_id ? (uint32_t)d.depo_id[j] : (uint32_t)j;
-  const uint32_t half_nt = (uint32_t)((g.pl[w.plane].nt + 1) >> 1);
+  const uint32_t half_nt = (uint32_t)((pl.nt + 1) >> 1);
   const Philox4 ph = philox4x32_10((uint32_t)b * half_nt + (uint32_t)(k >> 1), did, (uint32_t)w.key_event,
                                    (uint32_t)w.plane << 24, args->key0, args->key1);
   if (MODE == kModeNormal) {
@@ -178,8 +200,9 @@ __device__ __forceinline__ void row_weights(const RowWin& w, int b0, int b1, int
 // item's rows one at a time.  A wave draws a row's cells in tick pairs (cells (b, 2m) and
 // (b, 2m + 1) share a Philox block); binomial cells that are not surely 0 wait in LDS until 64
 // of one regime are together, whatever their rows, so a batch fills all lanes.
+#define WCT_DRAW_ARGS (const DrawArgs<T>*)(const void*)__builtin_amdgcn_kernarg_segment_ptr()
 template <typename T, int MODE, int TH, int TW>
-__global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(DrawArgs<T> args) {
+__global__ void __launch_bounds__(kDrawThreads, (draw_blocks<MODE, TH, TW>())) k_tile(DrawArgs<T> args) {
   const DepoView<T>& d = args.d;
   const RasterGeom& g = args.g;
   const int32_t* __restrict__ list = args.list;
@@ -188,22 +211,23 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
   int32_t* __restrict__ ctrl = args.ctrl;
   T* __restrict__ grid = args.grid;
   constexpr bool BINOM = MODE == kModeBinomial;
-  constexpr int NW = 4, WAIT = BINOM ? kWait : 1, UND = BINOM ? kUndecidedBinomial : kUndecidedNormal;
-  static_assert(TH * TW <= (1 << kDstBits), "a cell's tag holds its tile offset in kDstBits bits");
+  constexpr int NW = kDrawWaves, WAIT = BINOM ? kWait : 1, UND = BINOM ? kUndecidedBinomial : kUndecidedNormal;
+  static_assert(TH * TW - 1 <= (int)kEntryDst, "an entry holds the cell's tile offset");
   static_assert(TW % 2 == 0, "tick pairs do not straddle tiles");
   __shared__ uint32_t tile[TH * TW];
   __shared__ float s_a[NW][TH];
   __shared__ alignas(8) float s_b[NW][TW];
-  __shared__ uint32_t s_wait[NW][3 * WAIT];  // probability, uniform, tag
-  __shared__ uint32_t s_und[NW][UND];
-  __shared__ float s_n[kRowsPerItem];
+  __shared__ uint2 s_wait[NW][WAIT];  // wait_entry
+  __shared__ uint2 s_und[NW][UND];
+  __shared__ float s_n[kItemRows];
   __shared__ float s_sum[NW];
   __shared__ int s_item, s_row;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint32_t* const wait = s_wait[wv];
+  uint2* const wait = s_wait[wv];
   const int zgroup = zero_group(ntiles), nzero = (int)((ntiles + zgroup - 1) / zgroup);
   const int nitems = ctrl[kCtrlNItems];
   bool more_items = true;  // block-uniform
+  int nx = 0;              // undecided cells of this wave, kept across items
   for (int step = 0;; ++step) {
     if (threadIdx.x == 0) s_item = more_items ? next_item(ctrl, step == 0) : INT_MAX;
     __syncthreads();
@@ -214,22 +238,25 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
     if (!more_items && !more_zero) break;
     __syncthreads();  // every thread has read s_item
     if (more_items) {
-      const TileItem w_ = tile_item<TH, TW>(g, item, args.items, args.item_off, args.offs);
+      const TileItem w_ = tile_item<TH, TW>(g, item, args.items, args.item_off, args.offs, args.item_shift);
       const int tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
       const PlaneGeom& pl = g.pl[w_.plane];
       T* gp = grid + (int64_t)w_.ev * g.grid_ev_stride + pl.grid_off + (int64_t)tb0 * pl.nt + tk0;
-      for (int x = threadIdx.x; x < TH * TW; x += 256) tile[x] = 0;
+      for (int x = threadIdx.x; x < TH * TW; x += kDrawThreads) tile[x] = 0;
       // the rows' electron counts and their sum
       float n = 0.0f;
-      for (int x = threadIdx.x; x < r1 - r0; x += 256) n += (s_n[x] = electrons_of((double)d.q[list[r0 + x]]));
+      for (int x = threadIdx.x; x < r1 - r0; x += kDrawThreads) n += (s_n[x] = electrons_of((double)d.q[list[r0 + x]]));
   #pragma unroll
       for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
       if (lane == 0) s_sum[wv] = n;
       if (threadIdx.x == 0) s_row = r0;
       __syncthreads();
-      const bool direct = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) > kTileElectrons;  // block-uniform
+      float sum = 0.0f;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) sum += s_sum[v];
+      const bool direct = sum > kTileElectrons;  // block-uniform
       if (direct && w_.owned) {  // (a split tile is clear already)
-        for (int x = threadIdx.x; x < th * TW; x += 256)
+        for (int x = threadIdx.x; x < th * TW; x += kDrawThreads)
           if (x % TW < tw) gp[(int64_t)(x / TW) * pl.nt + x % TW] = T(0);
         __threadfence();
         __syncthreads();
@@ -241,53 +268,53 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
         else
           atomicAdd(&tile[o], (uint32_t)k);
       };
-      // waiting and undecided cells of this wave (wave-uniform counts)
-      int ni = 0, nc = 0, nx = 0;
-      auto leave = [&](bool undecided, uint32_t tag) {
+      // waiting cells of this wave (wave-uniform counts); the undecided ones below `old` are of
+      // earlier items, whose tiles are written
+      int ni = 0, nc = 0, old = nx;
+      const uint32_t tile_bits = undecided_tile(tb0 / TH, tk0 / TW);
+      auto leave = [&](bool undecided, uint32_t row, uint32_t dst) {
         const uint64_t mask = __builtin_amdgcn_ballot_w64(undecided);
-        if (undecided) s_und[wv][nx + lanes_below(mask)] = tag;
+        if (undecided) s_und[wv][nx + lanes_below(mask)] = make_uint2((uint32_t)list[r0 + (int)row], tile_bits | dst);
         nx += __popcll(mask);
       };
-      // runs whatever holds at least `least` cells, undecided ones first (they are then below
-      // 64 before a batch adds to them)
+      // runs the regimes that hold at least `least` cells, and undecided ones by 64 before that
+      // (they are then below 64 before a batch adds to them)
       auto run = [&](int least) {
         for (;;) {
-          if (nx >= least) {
-            const int take = min(nx, 64);
-            nx -= take;
+          if (nx >= 64) {
+            nx -= 64;
             wave_sync();
-            if (lane < take) {
-              const uint32_t tag = s_und[wv][nx + lane], o = tag & ((1u << kDstBits) - 1u);
-              const int64_t j = list[r0 + (int)(tag >> kDstBits)];
-              add(o, exact_count<T, MODE>(
-                         (const DrawArgs<T>*)(const void*)__builtin_amdgcn_kernarg_segment_ptr(), j,
-                         tb0 + (int)(o / TW), tk0 + (int)(o % TW)));
-            }
+            const uint2 cell = s_und[wv][nx + lane];
+            int64_t at;
+            const int k = exact_count<T, MODE, TH, TW>(WCT_DRAW_ARGS, cell, &at);
             wave_sync();
+            if (nx + lane >= old)
+              add(cell.y & kEntryDst, k);
+            else if (k > 0)
+              atomicAdd(grid + at, (T)k);
+            old = min(old, nx);
           } else if (BINOM && ni >= least) {
             const int take = min(ni, 64);
             ni -= take;
             wave_sync();
             const int at = ni + min(lane, take - 1);
-            const uint32_t tag = wait[2 * WAIT + at];
+            const uint2 q = wait[at];
             int k;
-            const bool sure =
-                fast_inversion(s_n[tag >> kDstBits], __uint_as_float(wait[at]), __uint_as_float(wait[WAIT + at]), &k);
+            const bool sure = fast_inversion(s_n[q.x & kEntryRow], entry_p(q.x), entry_u(q.y), &k);
             wave_sync();
-            if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
-            leave(lane < take && !sure, tag);
+            if (lane < take && sure) add(q.y & kEntryDst, k);
+            leave(lane < take && !sure, q.x & kEntryRow, q.y & kEntryDst);
           } else if (BINOM && nc >= least) {
             const int take = min(nc, 64);
             wave_sync();
             const int at = WAIT - nc + min(lane, take - 1);
             nc -= take;
-            const uint32_t tag = wait[2 * WAIT + at];
+            const uint2 q = wait[at];
             int k;
-            const bool sure =
-                fast_chopdown(s_n[tag >> kDstBits], __uint_as_float(wait[at]), __uint_as_float(wait[WAIT + at]), &k);
+            const bool sure = fast_chopdown(s_n[q.x & kEntryRow], entry_p(q.x), entry_u(q.y), &k);
             wave_sync();
-            if (lane < take && sure) add(tag & ((1u << kDstBits) - 1u), k);
-            leave(lane < take && !sure, tag);
+            if (lane < take && sure) add(q.y & kEntryDst, k);
+            leave(lane < take && !sure, q.x & kEntryRow, q.y & kEntryDst);
           } else {
             break;
           }
@@ -321,7 +348,8 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
         const uint32_t half_nt = (uint32_t)((pl.nt + 1) >> 1);
         int bi = lane / np, pj = lane - bi * np;
         uint32_t ctr = (uint32_t)(b0 + bi) * half_nt + (uint32_t)(m0 + pj);
-        uint32_t dst = (uint32_t)((b0 - tb0 + bi) * TW + 2 * (m0 + pj) - tk0) | ((uint32_t)(r - r0) << kDstBits);
+        uint32_t dst = (uint32_t)((b0 - tb0 + bi) * TW + 2 * (m0 + pj) - tk0);
+        const uint32_t row = (uint32_t)(r - r0);
         const uint32_t ctr_step = (uint32_t)dq * half_nt + (uint32_t)dr, ctr_wrap = half_nt - (uint32_t)np;
         const uint32_t dst_step = (uint32_t)(dq * TW + 2 * dr), dst_wrap = (uint32_t)(TW - 2 * np);
         for (int base = 0; base < total; base += 64) {
@@ -334,31 +362,31 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
             bw = wb[pj];
           }
           if constexpr (BINOM) {
-            float mu = a * bw.x, u = (float)ph.w0 * 0x1p-32f;
-            const float mu1 = a * bw.y, u1 = (float)ph.w2 * 0x1p-32f;
-            uint32_t tag = dst;
-  #pragma unroll 1
-            for (int half = 0; half < 2; ++half) {
-              const bool need = in && !(u + mu < zero_limit);
-              const bool top = need && mu >= (float)kMuSwitch;
-              const uint64_t mall = __builtin_amdgcn_ballot_w64(need), mtop = __builtin_amdgcn_ballot_w64(top);
-              const uint64_t mlow = mall & ~mtop;
-              if (mall) {
-                const int low = ni + lanes_below(mlow), high = WAIT - 1 - nc - lanes_below(mtop);
-                const int at = top ? high : low;
-                if (need) {
-                  wait[at] = __float_as_uint(mu * rN);
-                  wait[WAIT + at] = __float_as_uint(u);
-                  wait[2 * WAIT + at] = tag;
-                }
-                ni += __popcll(mlow);
-                nc += __popcll(mtop);
-                run(64);
-              }
-              mu = mu1;
-              u = u1;
-              tag = dst + 1;
+            const float mu[2] = {a * bw.x, a * bw.y};
+            const uint32_t w[2] = {ph.w0, ph.w2};
+            const int left = total - base;  // lanes that hold a pair
+            const uint64_t all = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+            uint64_t need[2], top[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              need[h] = __builtin_amdgcn_ballot_w64(!(fmaf((float)w[h], 0x1p-32f, mu[h]) < zero_limit)) & all;
+              top[h] = __builtin_amdgcn_ballot_w64(mu[h] >= (float)kMuSwitch) & need[h];
             }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              if (need[h] == 0) continue;
+              const uint64_t low = need[h] & ~top[h];
+              int at = ni + lanes_below(low);
+              if (top[h]) {
+                const int up = WAIT - 1 - nc - lanes_below(top[h]);
+                at = __builtin_amdgcn_inverse_ballot_w64(top[h]) ? up : at;
+              }
+              if (__builtin_amdgcn_inverse_ballot_w64(need[h]))
+                wait[at] = make_uint2(entry_x(mu[h] * rN, row), entry_y(w[h], dst + h));
+              ni += __popcll(low);
+              nc += __popcll(top[h]);
+            }
+            run(64);
           } else {
             float ze, zo;
             const bool ok = fast_normal_pair(ph.w0, ph.w1, ph.w2, &ze, &zo);
@@ -366,10 +394,10 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
             int ke, ko;
             const bool se = fast_normal_count(N, mue, mue * rN, ze, &ke) && ok;
             const bool so = fast_normal_count(N, muo, muo * rN, zo, &ko) && ok;
-            if (in && se) add(dst & ((1u << kDstBits) - 1u), ke);
-            if (in && so) add((dst & ((1u << kDstBits) - 1u)) + 1, ko);
-            leave(in && !se, dst);
-            leave(in && !so, dst + 1);
+            if (in && se) add(dst, ke);
+            if (in && so) add(dst + 1, ko);
+            leave(in && !se, row, dst);
+            leave(in && !so, row, dst + 1);
             run(64);
           }
           const bool wrap = pj + dr >= np;
@@ -385,7 +413,7 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
         constexpr int V = 16 / (int)sizeof(T);
         if (w_.owned && tw == TW && pl.nt % V == 0 && (reinterpret_cast<uintptr_t>(gp) & 15) == 0) {
           constexpr int VR = TW / V;  // 16-byte vectors per tile row
-          for (int x = threadIdx.x; x < th * VR; x += 256) {
+          for (int x = threadIdx.x; x < th * VR; x += kDrawThreads) {
             const int rr = x / VR, c = x - (x / VR) * VR;
             const uint32_t* src = &tile[rr * TW + c * V];
             T v[V];
@@ -394,7 +422,7 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
             *reinterpret_cast<float4*>(gp + (int64_t)rr * pl.nt + c * V) = *reinterpret_cast<const float4*>(v);
           }
         } else {
-          for (int x = threadIdx.x; x < th * TW; x += 256) {
+          for (int x = threadIdx.x; x < th * TW; x += kDrawThreads) {
             const int rr = x / TW, c = x - (x / TW) * TW;
             if (c < tw) {
               T* dst = gp + (int64_t)rr * pl.nt + c;
@@ -406,11 +434,19 @@ __global__ void __launch_bounds__(256, (draw_blocks<MODE, TH, TW>())) k_tile(Dra
           }
         }
       }
+      // the tile's stores have been served before another wave adds an undecided cell to it
+      __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
     }
     if (more_zero) clear_group<T, TH, TW>(g, zg, zgroup, ntiles, counts, args.hull, grid);
   }
+  if (lane < nx) {
+    int64_t at;
+    const int k = exact_count<T, MODE, TH, TW>(WCT_DRAW_ARGS, s_und[wv][lane], &at);
+    if (k > 0) atomicAdd(grid + at, (T)k);
+  }
 }
+#undef WCT_DRAW_ARGS
 
 template <typename T, int TH, int TW>
 hipError_t launch_tile_draw(const DepoView<T>& d, const RasterGeom& g, double nsigma, int mode, uint64_t seed, T* grid,
@@ -429,12 +465,13 @@ hipError_t launch_tile_draw(const DepoView<T>& d, const RasterGeom& g, double ns
   a.item_off = ws.item_off;
   a.counts = ws.counts;
   a.ntiles = ws.ntiles;
+  a.item_shift = ws.item_shift;
   a.ctrl = ws.ctrl;
   a.tables = tables;
   a.lf = lfact;
   a.hull = ws.hull;
 #define WCT_DRAW_LAUNCH(M) \
-  hipLaunchKernelGGL((k_tile<T, M, TH, TW>), dim3((unsigned)(n_cu * draw_blocks<M, TH, TW>())), dim3(256), 0, st, a)
+  hipLaunchKernelGGL((k_tile<T, M, TH, TW>), dim3((unsigned)(n_cu * draw_blocks<M, TH, TW>())), dim3(kDrawThreads), 0, st, a)
   if (mode == kModeBinomial)
     WCT_DRAW_LAUNCH(kModeBinomial);
   else

@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
                                                       const int32_t* __restrict__ offs,
                                                       const int32_t* __restrict__ items,
                                                       const int32_t* __restrict__ item_off,
-                                                      const int32_t* __restrict__ counts, int64_t ntiles,
+                                                      const int32_t* __restrict__ counts, int64_t ntiles, int item_shift,
                                                       int32_t* __restrict__ ctrl, const int2* __restrict__ hull) {
   constexpr int R = kMeanRows, RB = TH / 64, CB = TW / 16;
   constexpr int SA = mean_stride(TH), SB = mean_stride(TW);
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
     if (!more_items && !more_zero) break;
     __syncthreads();  // every thread has read s_item
     if (more_items) {
-      const TileItem w = tile_item<TH, TW>(g, item, items, item_off, offs);
+      const TileItem w = tile_item<TH, TW>(g, item, items, item_off, offs, item_shift);
       const PlaneGeom& pl = g.pl[w.plane];
       d4 acc[RB][CB];
 #pragma unroll
@@ -190,7 +190,7 @@ hipError_t launch_tile_mean(const DepoView<T>& d, const RasterGeom& g, double ns
   const dim3 blocks((unsigned)(n_cu * mean_blocks(TH, TW)));
 #define WCT_MEAN_LAUNCH(POLY)                                                                                       \
   hipLaunchKernelGGL((k_tile_mean<T, TH, TW, POLY>), blocks, dim3(256), 0, st, d, g, nsigma, grid, ws.list, ws.offs, \
-                     ws.items, ws.item_off, ws.counts, ws.ntiles, ws.ctrl, ws.hull)
+                     ws.items, ws.item_off, ws.counts, ws.ntiles, ws.item_shift, ws.ctrl, ws.hull)
   // the polynomial wherever its range holds the windows' edges, else the library's erf
   if (nsigma <= kErfPolyNsigma)
     WCT_MEAN_LAUNCH(true);

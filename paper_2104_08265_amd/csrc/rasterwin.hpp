@@ -168,7 +168,7 @@ struct TileItem {
 template <int TH, int TW>
 __device__ __forceinline__ TileItem tile_item(const RasterGeom& g, int item, const int32_t* __restrict__ items,
                                               const int32_t* __restrict__ item_off,
-                                              const int32_t* __restrict__ offs) {
+                                              const int32_t* __restrict__ offs, int item_shift) {
   TileItem w;
   w.t = items[item];
   const int chunk = item - item_off[w.t];
@@ -183,8 +183,8 @@ __device__ __forceinline__ TileItem tile_item(const RasterGeom& g, int item, con
   w.tk0 = tc * TW;
   w.th = min(TH, pl.nb - w.tb0);
   w.tw = min(TW, pl.nt - w.tk0);
-  w.r0 = offs[w.t] + chunk * kRowsPerItem;
-  w.r1 = min(offs[w.t] + (chunk + 1) * kRowsPerItem, offs[w.t + 1]);
+  w.r0 = offs[w.t] + (chunk << item_shift);
+  w.r1 = min(w.r0 + (1 << item_shift), offs[w.t + 1]);
   return w;
 }
 
