@@ -241,7 +241,11 @@ RasterGeom raster_geom(const wct_plan* P, int n_events, int event_base) {
   g.ntiles_ev = P->ntiles_ev;
   g.grid_ev_stride = P->grid_elems;
   g.rows_ev = P->rows_ev;
-  for (int p = 0; p < P->n_planes; ++p) g.pl[p] = P->geom[p];
+  for (int p = 0; p < P->n_planes; ++p) {
+    g.pl[p] = P->geom[p];
+    g.bit_off[p] = g.bits_ev;
+    g.bits_ev += (P->geom[p].nb + 31) / 32;
+  }
   return g;
 }
 
@@ -275,17 +279,17 @@ RasterWs carve_raster(const wct_plan* P, Carver& cv, int n_events, int64_t n_row
   RasterWs w;
   w.ntiles = (int64_t)n_events * P->ntiles_ev;
   const int64_t nrow = n_rows > 0 ? n_rows : 1;
-  const int64_t nsb = (w.ntiles + kScanPerBlock - 1) / kScanPerBlock;
+  w.n_rows = n_rows;
   w.ctrl = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (kCtrlWords + w.ntiles)));
   w.counts = w.ctrl ? w.ctrl + kCtrlWords : nullptr;
-  // the items (at most ntiles + 4 n / 2^kItemShiftMin) are written once the slots are used
-  w.rank = w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
-  cv.take(sizeof(int32_t) * (w.ntiles + (4 * nrow + 255) / 256 + 1));
+  w.rank = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
   w.offs = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
   w.item_off = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
+  // at most ntiles + 4 n / 2^kItemShiftMin items
+  w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + (4 * nrow + 255) / 256 + 1)));
+  cv.take(sizeof(int32_t) * nrow);
   w.list = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
-  w.big = static_cast<int32_t*>(cv.take(sizeof(int32_t) * nrow));
-  w.blocks = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 2 * (nsb > 0 ? nsb : 1)));
+  cv.take(sizeof(int32_t) * 2 * (w.ntiles > 4096 ? (w.ntiles + 4095) / 4096 : 1));
   return w;
 }
 
@@ -412,11 +416,12 @@ DepoView<T> view(const wct_depos* d) {
 // Launch sequences -------------------------------------------------------------------
 template <typename T>
 int run_raster(wct_plan* P, const wct_depos* d, const wct_opts* o, T* grid, Carver& cv, hipStream_t st,
-               int2* span = nullptr, int2* hull = nullptr) {
+               int2* span = nullptr, int2* hull = nullptr, uint32_t* bits = nullptr) {
   const RasterGeom g = raster_geom(P, o->n_events, o->event_base);
   RasterWs ws = carve_raster(P, cv, o->n_events, d->n);
   ws.span = span;
   ws.hull = hull;
+  ws.bits = bits;
   HIP_TRY(launch_raster<T>(view<T>(d), g, o->nsigma, o->fluctuate, o->seed, grid, ws, P->d_tables, P->d_lfact,
                            P->n_cu, st, hook(P), P->tile),
           "raster launch");
@@ -426,11 +431,11 @@ int run_raster(wct_plan* P, const wct_depos* d, const wct_opts* o, T* grid, Carv
 
 // span (optional): the raster's row tick spans of these events; the row transform then
 // skips the work (not the zero output) of rows, or row pairs, that no window reached, and
-// reads the others only inside their spans.  tiles (optional, with span): room for the
-// direct column pass's tile flags of these events; a plane on the direct pass then skips
-// the tiles no row reaches (zero M^ without reading S^), and its row transform does not
-// write the zero spectra that only such tiles would read.  wires (optional, with tiles):
-// room for the per-wire flags; on a plane of the direct column pass without noise, the
+// reads the others only inside their spans.  With it: rbits, the raster's row flags, and
+// tiles, room for the direct column pass's tile flags of these events; a plane on the direct
+// pass then skips the tiles no row reaches (zero M^ without reading S^), and its row transform
+// does not write the zero spectra that only such tiles would read; and wires, room for the
+// per-wire flags; on a plane of the direct column pass without noise, the
 // inverse row transform writes the zero waveform of a wire no window reaches within the
 // response's reach (its M^ is exactly zero there) without transforming it.
 template <typename T>
@@ -441,10 +446,8 @@ int run_convolve(wct_plan* P, const T* grid, int n_events, T* wave, Carver& cv, 
   cx<T>* shat = static_cast<cx<T>*>(c.shat);
   cx<T>* mhat = static_cast<cx<T>*>(c.mhat);
   const WireTileGeom tg = wire_tile_geom(P);
-  const bool flags = span && tiles;
-  if (flags) HIP_TRY(launch_wire_tiles(tg, n_events, span, tiles, st), "tile flag launch");
-  if (flags && wires) HIP_TRY(launch_wire_live(tg, n_events, span, wires, st), "wire flag launch");
-  if (flags && rbits) HIP_TRY(launch_row_bits(tg, n_events, span, rbits, st), "row flag launch");
+  const bool flags = span && tiles && wires && rbits;
+  if (flags) HIP_TRY(launch_reach(tg, n_events, rbits, tiles, wires, st), "reach flag launch");
   for (int p = 0; p < P->n_planes; ++p) {
     const PlaneGeom& G = P->geom[p];
     const cx<T>* tw_t = static_cast<const cx<T>*>(P->tw_t[p]);
@@ -457,7 +460,7 @@ int run_convolve(wct_plan* P, const T* grid, int n_events, T* wave, Carver& cv, 
       wt.live = tiles + tg.tile_off[p];
       wt.ev_stride = tg.tiles_ev;
       wt.ntile = tg.tile_off[p + 1] - tg.tile_off[p];
-      if (rbits && G.I <= 10) {
+      if (G.I <= 10) {
         wt.rowbits = rbits + tg.bit_off[p];
         wt.bits_ev = tg.bits_ev;
       }
@@ -486,7 +489,7 @@ int run_convolve(wct_plan* P, const T* grid, int n_events, T* wave, Carver& cv, 
       nz.event_base = noise->event_base;
     }
     WireLive wl;
-    if (flags && wires && P->wire_direct[p] && !nz.amp) {
+    if (flags && P->wire_direct[p] && !nz.amp) {
       wl.live = wires + tg.wire_off[p];
       wl.ev_stride = tg.wires_ev;
     }
@@ -1366,11 +1369,11 @@ static int simulate_enqueue(wct_plan* plan, const wct_depos* depos, const wct_op
     Carver cr(static_cast<char*>(ws) + rest), cc(static_cast<char*>(ws) + rest);
     char* w = static_cast<char*>(wave) + plan->esize * (size_t)e0 * plan->wave_elems;
     if (plan->dtype == WCT_F32) {
-      if ((rc = run_raster<float>(plan, depos, &sub, static_cast<float*>(grid), cr, st, span, hull))) return rc;
+      if ((rc = run_raster<float>(plan, depos, &sub, static_cast<float*>(grid), cr, st, span, hull, rbits))) return rc;
       rc = run_convolve<float>(plan, static_cast<const float*>(grid), sub.n_events, reinterpret_cast<float*>(w), cc,
                                st, span, &sub, tiles, wires, rbits);
     } else {
-      if ((rc = run_raster<double>(plan, depos, &sub, static_cast<double*>(grid), cr, st, span, hull))) return rc;
+      if ((rc = run_raster<double>(plan, depos, &sub, static_cast<double*>(grid), cr, st, span, hull, rbits))) return rc;
       rc = run_convolve<double>(plan, static_cast<const double*>(grid), sub.n_events, reinterpret_cast<double*>(w),
                                 cc, st, span, &sub, tiles, wires, rbits);
     }

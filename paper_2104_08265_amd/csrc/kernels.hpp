@@ -24,6 +24,7 @@ struct RasterGeom {
   int ntiles_ev;           // raster tiles per event
   int64_t grid_ev_stride;  // grid elements per event
   int64_t rows_ev;         // impact rows per event (all planes)
+  int bits_ev, bit_off[kMaxPlanes];  // 32-row words of the row flags per event, each plane's first
   PlaneGeom pl[kMaxPlanes];
 };
 
@@ -39,7 +40,6 @@ constexpr int kQueues = 8, kQueueStride = 32;  // one queue per XCD, each head o
 // Rows one tile work item processes at most: 2^shift, chosen per call (item_shift).
 constexpr int kItemShiftMin = 4, kItemShiftMax = 8;
 constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kernels at most
-constexpr int kScanPerBlock = 4096;
 
 // Raster tile variants: X(real type, TH rows, TW ticks, tile-kernel blocks per CU).
 // Tall tiles: a window of up to 129 impact rows (sigma_p <= 2 pitches at 3 sigma) spans
@@ -73,16 +73,16 @@ inline const TileVariantDesc* tile_variants(int* count) {
 struct RasterWs {
   int32_t* ctrl;      // kCtrlWords
   int32_t* counts;    // [ntiles]
-  int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches (until k_fill)
-  int32_t* offs;      // [ntiles + 1]
-  int32_t* item_off;  // [ntiles + 1]
-  int32_t* items;     // over rank and the room behind it: at least 4 n + ntiles
-  int32_t* list;      // [4 n]
-  int32_t* big;       // [n]
-  int32_t* blocks;    // [2 * nscan_blocks]
+  int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches
+  int32_t* offs;      // [ntiles]: a touched tile's slice of the row list
+  int32_t* item_off;  // [ntiles]: its first work item
+  int32_t* items;     // [ntiles + n and more]: the work items' tiles
+  int32_t* list;      // [4 n]; its end holds the wide rows, which have no entries in it
   int64_t ntiles;
   int item_shift;
+  int64_t n_rows;
   int2* span = nullptr;  // optional [event][rows_ev] tick spans of the rows (row_span)
+  uint32_t* bits = nullptr;  // with span: [event][bits_ev], the rows some window reaches
   int2* hull = nullptr;  // with span: [event][bands] tile-column hull of each band of TH rows
 };
 
@@ -214,8 +214,8 @@ template <typename T>
 hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, const cx<T>* rtick, cx<T>* mhat,
                                  int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, hipStream_t st,
                                  const WireTiles& wt = WireTiles());
-// The direct pass's tile flags of every plane and event from the row spans: plane p's
-// tiles start at tile_off[p] of an event's tiles_ev.
+// From the row flags: the direct pass's tile flags of every plane and event (plane p's
+// tiles start at tile_off[p] of an event's tiles_ev),
 struct WireTileGeom {
   int n_planes, tiles_ev, wires_ev;
   int64_t rows_ev;
@@ -223,11 +223,10 @@ struct WireTileGeom {
   int64_t row_off[kMaxPlanes];
   int bits_ev, bit_off[kMaxPlanes + 1];  // 32-row words of the row flags per event, per plane
 };
-hipError_t launch_row_bits(const WireTileGeom& g, int n_events, const int2* span, uint32_t* bits, hipStream_t st);
-hipError_t launch_wire_tiles(const WireTileGeom& g, int n_events, const int2* span, uint8_t* live, hipStream_t st);
-// The per-wire flags of WireLive for every plane and event ([event][wires_ev], plane p's
-// wires from wire_off[p]).
-hipError_t launch_wire_live(const WireTileGeom& g, int n_events, const int2* span, uint8_t* live, hipStream_t st);
+// and the per-wire flags of WireLive for every plane and event ([event][wires_ev], plane
+// p's wires from wire_off[p]).
+hipError_t launch_reach(const WireTileGeom& g, int n_events, const uint32_t* bits, uint8_t* tiles, uint8_t* wires,
+                        hipStream_t st);
 template <typename T>
 hipError_t launch_colpass_adj_direct(const cx<T>* ghat, int64_t ghat_ev_stride, const cx<T>* rtick, cx<T>* hhat,
                                      int64_t hhat_ev_stride, int nw, int nphase, int nchunk, int n_events,

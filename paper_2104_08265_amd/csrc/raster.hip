@@ -7,15 +7,16 @@
 //                  to a separate list handled in 64 x 64 chunks with global atomics, k_big)
 //                  and keeps the value each increment returns, its slot in that tile's
 //                  row list; optionally it marks the impact rows its window reaches;
-//  2. scan       - exclusive prefix sums give each tile its slice of a row list and
-//                  a number of work items (of up to 2^item_shift rows; 0 for an empty tile);
+//  2. k_plan     - each touched tile gets its slice of a row list and a number of work items
+//                  (of up to 2^item_shift rows); optionally the rows' tick spans;
 //  3. k_fill     - rows are written into their tiles' slices at their slots (plain stores);
+//                  tiles of several work items are cleared;
 //  4. the tile kernel (rastermean.hip for the mean, rasterdraw.hip for drawn counts) - persistent
 //                  blocks take work items from striped queues (next_item) and, in step, groups
 //                  of consecutive tiles to clear; a work item accumulates its rows' in-tile
 //                  sub-patches and then writes the tile: plain stores when the tile has one
 //                  item, global atomic adds when a crowded tile was split across items (those
-//                  tiles are cleared first by k_zero_split); a group's tiles that no row touches
+//                  tiles are cleared first by k_fill); a group's tiles that no row touches
 //                  are cleared with plain stores, so the grid needs no separate clearing.
 // Window bounds are formed in FP64 exactly as the oracle forms them, so both sides
 // agree on which cells a row touches; fluctuated counts use the deterministic
@@ -238,6 +239,12 @@ __device__ __forceinline__ void patch_cells(const RowWin& w, int b0, int b1, int
   wave_sync();
 }
 
+// Up to three ranges cleared in one launch.
+__global__ void k_clear3(int32_t* a, int64_t na, int32_t* b, int64_t nb, int32_t* c, int64_t nc) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < na + nb + nc; i += (int64_t)gridDim.x * blockDim.x)
+    *(i < na ? a + i : i < na + nb ? b + (i - na) : c + (i - na - nb)) = 0;
+}
+
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -255,8 +262,8 @@ constexpr int kCountSlots = 2048;
 template <typename T, int TH, int TW>
 __global__ void __launch_bounds__(kCountBlock) k_count(DepoView<T> d, RasterGeom g, double nsigma,
                                                        int32_t* __restrict__ counts, int32_t* __restrict__ rank,
-                                                       int32_t* __restrict__ big, int32_t* __restrict__ ctrl,
-                                                       int2* __restrict__ span, int2* __restrict__ hull) {
+                                                       int32_t* __restrict__ list, int32_t* __restrict__ ctrl,
+                                                       uint32_t* __restrict__ bits, int2* __restrict__ hull) {
   static_assert(kCountSlots > 4 * kCountBlock && (kCountSlots & (kCountSlots - 1)) == 0, "count table size");
   __shared__ int32_t s_key[kCountSlots];  // tile index, -1 = free
   __shared__ int32_t s_cnt[kCountSlots];  // rows of this block in the tile, then their first slot
@@ -274,14 +281,17 @@ __global__ void __launch_bounds__(kCountBlock) k_count(DepoView<T> d, RasterGeom
       const PlaneGeom& pl = g.pl[w.plane];
       const int tr0 = w.b0 / TH, tr1 = (w.b1 - 1) / TH, tc0 = w.k0 / TW, tc1 = (w.k1 - 1) / TW;
       const bool wide = (tr1 - tr0 + 1) * (tc1 - tc0 + 1) > 4;
-      if (span) {
-        // The impact rows this window reaches are marked (span hi >= 1); they get their
-        // band's tile hull afterwards (k_band_spans).  Test first, so that neighbouring
-        // depositions do not contend.  A wide row, which no tile counts, widens the hulls
-        // of its bands itself (these rows are few).
-        int2* f = span + (int64_t)w.event * g.rows_ev + pl.row_off;
-        for (int b = w.b0; b < w.b1; ++b)
-          if (f[b].y == 0) atomicMax(&f[b].y, 1);
+      if (bits) {
+        // The impact rows this window reaches are marked, 32 to a word.  Test first, so that
+        // neighbouring depositions do not contend.  A wide row, which no tile counts, widens
+        // the hulls of its bands itself (these rows are few).
+        uint32_t* f = bits + (int64_t)w.event * g.bits_ev + g.bit_off[w.plane];
+        for (int wd = w.b0 >> 5; wd <= (w.b1 - 1) >> 5; ++wd) {
+          uint32_t m = ~0u;
+          if (wd == w.b0 >> 5) m &= ~0u << (w.b0 & 31);
+          if (wd == (w.b1 - 1) >> 5) m &= ~0u >> (31 - ((w.b1 - 1) & 31));
+          if ((f[wd] & m) != m) atomicOr(&f[wd], m);
+        }
         if (wide) {
           int bands_ev = 0;
           for (int q = 0; q < g.n_planes; ++q) bands_ev += g.pl[q].ntr;
@@ -293,7 +303,7 @@ __global__ void __launch_bounds__(kCountBlock) k_count(DepoView<T> d, RasterGeom
         }
       }
       if (wide) {
-        big[atomicAdd(&ctrl[kCtrlNBig], 1)] = (int32_t)j;
+        list[4 * d.n - 1 - atomicAdd(&ctrl[kCtrlNBig], 1)] = (int32_t)j;
       } else {
         const int64_t base = (int64_t)w.event * g.ntiles_ev + pl.tile_off;
         for (int tr = tr0; tr <= tr1; ++tr)
@@ -323,23 +333,83 @@ __global__ void __launch_bounds__(kCountBlock) k_count(DepoView<T> d, RasterGeom
   }
 }
 
-// 1b. row tick spans from the tiles (wct_simulate) -----------------------------
-// One block per band of TH impact rows (one tile row of a plane): the band's tiles that
-// some row reaches (a tile row's count, or a wide row's window) form the hull of tile
-// columns [lo, hi]; ticks [TW lo, TW (hi + 1)) hold every nonzero cell of the band, so the
-// band's marked rows take that span.  The hull is kept ({2^30 - lo, hi + 1}) for the tile
-// kernel, which clears only the empty tiles inside it: the row transform reads nothing
-// else.  Rows no window reached keep {0, 0}.
+// 2. what the tiles' counts decide, in one launch ------------------------------------
+// Blocks [0, tile_blocks): kPlanTiles tiles each.  A touched tile gets a slice of the row
+// list and its work items (of up to 2^shift rows).  The slices' order does not matter, so a
+// block takes its share of the list and of the items with one atomic add each, where three
+// scan launches and one for the items kept tile order (18 us on the three-plane detector).
+// The blocks after them, one per band of TH impact rows (one tile row of a plane), with
+// spans: the band's tiles that some row reaches (a tile row's count, or a wide row's window)
+// form the hull of tile columns [lo, hi]; ticks [TW lo, TW (hi + 1)) hold every nonzero cell
+// of the band, so the band's marked rows take that span and its other rows {0, 0}.  The hull
+// is kept ({2^30 - lo, hi + 1}) for the tile kernel, which clears only the empty tiles
+// inside it: the row transform reads nothing else.
+constexpr int kPlanTiles = 1024;
+
+__device__ __forceinline__ int items_of(int c, int shift) { return (c + (1 << shift) - 1) >> shift; }
+
+__device__ __forceinline__ void plan_tiles(int64_t base, const int32_t* __restrict__ counts, int64_t ntiles, int shift,
+                                           int32_t* __restrict__ offs, int32_t* __restrict__ item_off,
+                                           int32_t* __restrict__ items, int32_t* __restrict__ ctrl) {
+  __shared__ int2 s_wave[4];
+  __shared__ int2 s_base;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int c[4];
+  int2 v = make_int2(0, 0);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int64_t t = base + 4 * threadIdx.x + e;
+    c[e] = t < ntiles ? counts[t] : 0;
+    v.x += c[e];
+    v.y += items_of(c[e], shift);
+  }
+  int2 incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int ax = __shfl_up(incl.x, o, 64), ay = __shfl_up(incl.y, o, 64);
+    if (lane >= o) {
+      incl.x += ax;
+      incl.y += ay;
+    }
+  }
+  if (lane == 63) s_wave[wv] = incl;
+  __syncthreads();
+  int2 before = make_int2(incl.x - v.x, incl.y - v.y), all = make_int2(0, 0);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wv) {
+      before.x += s_wave[w].x;
+      before.y += s_wave[w].y;
+    }
+    all.x += s_wave[w].x;
+    all.y += s_wave[w].y;
+  }
+  if (threadIdx.x == 0 && all.x > 0)
+    s_base = make_int2(atomicAdd(&ctrl[kCtrlTotal], all.x), atomicAdd(&ctrl[kCtrlNItems], all.y));
+  __syncthreads();
+  if (all.x == 0) return;
+  int row = s_base.x + before.x, item = s_base.y + before.y;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (c[e] == 0) continue;
+    const int64_t t = base + 4 * threadIdx.x + e;
+    offs[t] = row;
+    item_off[t] = item;
+    row += c[e];
+    for (const int end = item + items_of(c[e], shift); item < end; ++item) items[item] = (int32_t)t;
+  }
+}
+
 template <int TH, int TW>
-__global__ void __launch_bounds__(256) k_band_spans(RasterGeom g, const int32_t* __restrict__ counts,
-                                                     int bands_ev, int2* __restrict__ span, int2* __restrict__ hull) {
+__device__ __forceinline__ void band_spans(const RasterGeom& g, int band, const int32_t* __restrict__ counts,
+                                           int bands_ev, const uint32_t* __restrict__ bits, int2* __restrict__ span,
+                                           int2* __restrict__ hull) {
   __shared__ int s_lo[4], s_hi[4];
-  const int ev = blockIdx.x / bands_ev;
-  int bin = blockIdx.x - ev * bands_ev;
+  const int ev = band / bands_ev;
+  int tr = band - ev * bands_ev;
   int p = 0;
-  while (p + 1 < g.n_planes && bin >= g.pl[p].ntr) bin -= g.pl[p++].ntr;
+  while (p + 1 < g.n_planes && tr >= g.pl[p].ntr) tr -= g.pl[p++].ntr;
   const PlaneGeom& pl = g.pl[p];
-  const int tr = bin;
   const int32_t* cnt = counts + (int64_t)ev * g.ntiles_ev + pl.tile_off + (int64_t)tr * pl.ntc;
   int lo = INT_MAX, hi = -1;
   for (int tc = threadIdx.x; tc < pl.ntc; tc += 256)
@@ -360,8 +430,8 @@ __global__ void __launch_bounds__(256) k_band_spans(RasterGeom g, const int32_t*
   __syncthreads();
   lo = min(min(s_lo[0], s_lo[1]), min(s_lo[2], s_lo[3]));
   hi = max(max(s_hi[0], s_hi[1]), max(s_hi[2], s_hi[3]));
-  int2* hb = hull + blockIdx.x;  // [event][band]: blockIdx.x = ev * bands_ev + band
-  const int2 wide = *hb;         // the wide rows' tile columns, {2^30 - lo, hi + 1} or {0, 0}
+  int2* hb = hull + band;  // [event][band]
+  const int2 wide = *hb;   // the wide rows' tile columns, {2^30 - lo, hi + 1} or {0, 0}
   if (wide.y > 0) {
     lo = min(lo, kSpanBase - wide.x);
     hi = max(hi, wide.y - 1);
@@ -370,120 +440,48 @@ __global__ void __launch_bounds__(256) k_band_spans(RasterGeom g, const int32_t*
   if (threadIdx.x == 0) *hb = hi >= 0 ? make_int2(kSpanBase - lo, hi + 1) : make_int2(0, 0);
   const int klo = hi >= 0 ? lo * TW : 0, khi = hi >= 0 ? min((hi + 1) * TW, pl.nt) : 0;
   int2* f = span + (int64_t)ev * g.rows_ev + pl.row_off;
+  const uint32_t* fb = bits + (int64_t)ev * g.bits_ev + g.bit_off[p];
   const int b1 = min((tr + 1) * TH, pl.nb);
   for (int b = tr * TH + threadIdx.x; b < b1; b += 256)
-    if (f[b].y != 0) f[b] = make_int2(kSpanBase - klo, khi);
+    f[b] = (fb[b >> 5] >> (b & 31)) & 1u ? make_int2(kSpanBase - klo, khi) : make_int2(0, 0);
 }
 
-// 2. scan of (rows, items) per tile -------------------------------------------
-// Tiles no row touches get no work item: the tile kernel clears them in groups.
-__device__ __forceinline__ int items_of(int c, int shift) { return (c + (1 << shift) - 1) >> shift; }
-
-// Inclusive block scan of int2 over 1024 threads (16 waves of 64).
-__device__ int2 block_scan_incl(int2 v, int2* s_wave) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int ax = __shfl_up(v.x, o, 64), ay = __shfl_up(v.y, o, 64);
-    if (lane >= o) {
-      v.x += ax;
-      v.y += ay;
-    }
-  }
-  if (lane == 63) s_wave[wv] = v;
-  __syncthreads();
-  if (wv == 0) {
-    const int nw = blockDim.x >> 6;
-    int2 t = lane < nw ? s_wave[lane] : make_int2(0, 0);
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int ax = __shfl_up(t.x, o, 64), ay = __shfl_up(t.y, o, 64);
-      if (lane >= o) {
-        t.x += ax;
-        t.y += ay;
-      }
-    }
-    if (lane < nw) s_wave[lane] = t;
-  }
-  __syncthreads();
-  if (wv > 0) {
-    v.x += s_wave[wv - 1].x;
-    v.y += s_wave[wv - 1].y;
-  }
-  return v;
+template <int TH, int TW>
+__global__ void __launch_bounds__(256) k_plan(RasterGeom g, const int32_t* __restrict__ counts, int64_t ntiles,
+                                              int shift, int tile_blocks, int32_t* __restrict__ offs,
+                                              int32_t* __restrict__ item_off, int32_t* __restrict__ items,
+                                              int32_t* __restrict__ ctrl, int bands_ev,
+                                              const uint32_t* __restrict__ bits, int2* __restrict__ span,
+                                              int2* __restrict__ hull) {
+  if ((int)blockIdx.x < tile_blocks)
+    plan_tiles((int64_t)blockIdx.x * kPlanTiles, counts, ntiles, shift, offs, item_off, items, ctrl);
+  else
+    band_spans<TH, TW>(g, (int)blockIdx.x - tile_blocks, counts, bands_ev, bits, span, hull);
 }
 
-__global__ void __launch_bounds__(1024) k_scan_local(const int32_t* __restrict__ counts, int64_t n, int shift,
-                                                     int2* __restrict__ blocks) {
-  __shared__ int2 s_wave[16];
-  const int64_t base = (int64_t)blockIdx.x * kScanPerBlock + threadIdx.x * 4;
-  int2 s = make_int2(0, 0);
-  for (int e = 0; e < 4; ++e)
-    if (base + e < n) {
-      const int c = counts[base + e];
-      s.x += c;
-      s.y += items_of(c, shift);
-    }
-  const int2 incl = block_scan_incl(s, s_wave);
-  if (threadIdx.x == blockDim.x - 1) blocks[blockIdx.x] = incl;
-}
-
-__global__ void __launch_bounds__(1024) k_scan_blocks(int2* __restrict__ blocks, int nblocks,
-                                                      int32_t* __restrict__ ctrl) {
-  __shared__ int2 s_wave[16];
-  __shared__ int2 s_carry;
-  if (threadIdx.x == 0) s_carry = make_int2(0, 0);
-  __syncthreads();
-  for (int b0 = 0; b0 < nblocks; b0 += blockDim.x) {
-    const int b = b0 + threadIdx.x;
-    const int2 v = b < nblocks ? blocks[b] : make_int2(0, 0);
-    const int2 incl = block_scan_incl(v, s_wave);
-    const int2 carry = s_carry;
-    if (b < nblocks) blocks[b] = make_int2(carry.x + incl.x - v.x, carry.y + incl.y - v.y);  // exclusive
-    __syncthreads();
-    if (threadIdx.x == blockDim.x - 1) s_carry = make_int2(carry.x + incl.x, carry.y + incl.y);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    ctrl[kCtrlTotal] = s_carry.x;
-    ctrl[kCtrlNItems] = s_carry.y;
-  }
-}
-
-__global__ void __launch_bounds__(1024) k_scan_apply(const int32_t* __restrict__ counts, int64_t n, int shift,
-                                                     const int2* __restrict__ blocks, int32_t* __restrict__ offs,
-                                                     int32_t* __restrict__ item_off) {
-  __shared__ int2 s_wave[16];
-  const int64_t base = (int64_t)blockIdx.x * kScanPerBlock + threadIdx.x * 4;
-  int c[4];
-  int2 s = make_int2(0, 0);
-  for (int e = 0; e < 4; ++e) {
-    c[e] = base + e < n ? counts[base + e] : 0;
-    s.x += c[e];
-    s.y += base + e < n ? items_of(c[e], shift) : 0;
-  }
-  const int2 incl = block_scan_incl(s, s_wave);
-  const int2 bo = blocks[blockIdx.x];
-  int2 run = make_int2(bo.x + incl.x - s.x, bo.y + incl.y - s.y);
-  for (int e = 0; e < 4; ++e) {
-    const int64_t t = base + e;
-    if (t < n) {
-      offs[t] = run.x;
-      item_off[t] = run.y;
-      run.x += c[e];
-      run.y += items_of(c[e], shift);
-      if (t == n - 1) {
-        offs[n] = run.x;
-        item_off[n] = run.y;
-      }
-    }
-  }
-}
-
-// 3. rows into tile slices; 4a. item -> tile map; 4b. clear split tiles -------
+// 3. rows into tile slices (the first fill_blocks blocks); the others clear the tiles that
+// several work items accumulate into, a block's tiles gridDim apart (crowded tiles are
+// neighbours) ------------------------------------------------------------------------
+constexpr int kSplitBlocks = 1024;
 template <typename T, int TH, int TW>
-__global__ void k_fill(DepoView<T> d, RasterGeom g, double nsigma, const int32_t* __restrict__ offs,
-                       const int32_t* __restrict__ rank, int32_t* __restrict__ list) {
+__global__ void __launch_bounds__(256) k_fill(DepoView<T> d, RasterGeom g, double nsigma, int fill_blocks,
+                                              const int32_t* __restrict__ offs, const int32_t* __restrict__ rank,
+                                              int32_t* __restrict__ list, const int32_t* __restrict__ counts,
+                                              int64_t ntiles, int shift, T* __restrict__ grid) {
+  if ((int)blockIdx.x >= fill_blocks) {
+    __shared__ int s_n;
+    __shared__ int64_t s_t[256];
+    for (int64_t t0 = (int)blockIdx.x - fill_blocks; t0 < ntiles; t0 += (int64_t)256 * kSplitBlocks) {
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      const int64_t t = t0 + (int64_t)threadIdx.x * kSplitBlocks;
+      if (t < ntiles && counts[t] > (1 << shift)) s_t[atomicAdd(&s_n, 1)] = t;
+      __syncthreads();
+      for (int i = 0; i < s_n; ++i) zero_tile<T, TH, TW>(g, s_t[i], grid);
+      __syncthreads();
+    }
+    return;
+  }
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (j >= d.n) return;
   const RowWin w = row_window(d, j, g, nsigma);
@@ -500,24 +498,10 @@ __global__ void k_fill(DepoView<T> d, RasterGeom g, double nsigma, const int32_t
     }
 }
 
-__global__ void k_items(const int32_t* __restrict__ item_off, int64_t ntiles, int32_t* __restrict__ items) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= ntiles) return;
-  for (int k = item_off[t]; k < item_off[t + 1]; ++k) items[k] = (int32_t)t;
-}
-
-// Tiles that several work items accumulate into start from zero.
-template <typename T, int TH, int TW>
-__global__ void k_zero_split(RasterGeom g, const int32_t* __restrict__ counts, int64_t ntiles, int shift,
-                             T* __restrict__ grid) {
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x)
-    if (counts[t] > (1 << shift)) zero_tile<T, TH, TW>(g, t, grid);
-}
-
 // 5. rows wider than 4 tiles: 64 x 64 chunks per wave, straight to global atomics ------
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256, 3) k_big(DepoView<T> d, RasterGeom g, double nsigma, uint64_t seed,
-                                             T* __restrict__ grid, const int32_t* __restrict__ big,
+                                             T* __restrict__ grid, const int32_t* __restrict__ list,
                                              const int32_t* __restrict__ ctrl, const DetTables* __restrict__ tables,
                                              const double* __restrict__ lf) {
   constexpr int NWAVE = 4, CB = 64, CK = 64;
@@ -533,7 +517,7 @@ __global__ void __launch_bounds__(256, 3) k_big(DepoView<T> d, RasterGeom g, dou
   const int nbig = ctrl[kCtrlNBig];
   const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
   for (int r = blockIdx.x; r < nbig; r += gridDim.x) {
-    const int64_t j = __builtin_amdgcn_readfirstlane(big[r]);
+    const int64_t j = __builtin_amdgcn_readfirstlane(list[4 * d.n - 1 - r]);
     const RowWin w = row_window(d, j, g, nsigma);
     if (!w.ok) continue;
     const PlaneGeom& pl = g.pl[w.plane];
@@ -589,47 +573,34 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
   if (nt >= INT32_MAX) return hipErrorInvalidValue;  // tile indices and list offsets are int32
   ws.item_shift = item_shift(d.n, mode, n_cu);
   if (prof) prof->begin("raster_bin", st);
-  // control words and counts are contiguous
-  hipError_t e = launch_fill_i32(ws.ctrl, kCtrlWords + nt, 0, st);
-  if (e != hipSuccess) return e;
   const int bands_ev = bands_before(g, g.n_planes);
-  if (ws.span && !ws.hull) return hipErrorInvalidValue;  // spans come with band hulls
-  if (ws.span) {
-    e = launch_fill_i32(reinterpret_cast<int32_t*>(ws.hull), 2 * (int64_t)g.n_events * bands_ev, 0, st);
-    if (e != hipSuccess) return e;
-    e = launch_fill_i32(reinterpret_cast<int32_t*>(ws.span), 2 * g.n_events * g.rows_ev, 0, st);
-    if (e != hipSuccess) return e;
-  }
-  const unsigned rblocks = (unsigned)((d.n + 255) / 256);
+  if (ws.span && (!ws.hull || !ws.bits)) return hipErrorInvalidValue;  // spans come with hulls and row flags
+  // control words and counts are contiguous
+  const int64_t n_clear = kCtrlWords + nt, n_hull = ws.span ? 2 * (int64_t)g.n_events * bands_ev : 0;
+  const int64_t n_bits = ws.span ? (int64_t)g.n_events * g.bits_ev : 0;
+  const int64_t clear_blocks = (n_clear + n_hull + n_bits + 255) / 256;
+  hipLaunchKernelGGL(k_clear3, dim3((unsigned)(clear_blocks < 4096 ? clear_blocks : 4096)), dim3(256), 0, st, ws.ctrl,
+                     n_clear, reinterpret_cast<int32_t*>(ws.hull), n_hull, reinterpret_cast<int32_t*>(ws.bits), n_bits);
+  WCT_CHECK_LAUNCH();
   if (d.n > 0) {
     hipLaunchKernelGGL((k_count<T, TH, TW>), dim3((unsigned)((d.n + kCountBlock - 1) / kCountBlock)),
-                       dim3(kCountBlock), 0, st, d, g, nsigma, ws.counts, ws.rank, ws.big, ws.ctrl, ws.span,
-                       ws.hull);
+                       dim3(kCountBlock), 0, st, d, g, nsigma, ws.counts, ws.rank, ws.list, ws.ctrl,
+                       ws.span ? ws.bits : nullptr, ws.hull);
     WCT_CHECK_LAUNCH();
   }
-  if (ws.span) {
-    hipLaunchKernelGGL((k_band_spans<TH, TW>), dim3((unsigned)(g.n_events * bands_ev)), dim3(256), 0, st, g,
-                       ws.counts, bands_ev, ws.span, ws.hull);
-    WCT_CHECK_LAUNCH();
-  }
-  const int nsb = (int)((nt + kScanPerBlock - 1) / kScanPerBlock);
-  int2* blocks = reinterpret_cast<int2*>(ws.blocks);
-  hipLaunchKernelGGL(k_scan_local, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, ws.item_shift, blocks);
-  WCT_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, blocks, nsb, ws.ctrl);
-  WCT_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(1024), 0, st, ws.counts, nt, ws.item_shift, blocks, ws.offs, ws.item_off);
+  const int tile_blocks = (int)((nt + kPlanTiles - 1) / kPlanTiles);
+  hipLaunchKernelGGL((k_plan<TH, TW>), dim3((unsigned)(tile_blocks + (ws.span ? g.n_events * bands_ev : 0))), dim3(256),
+                     0, st, g, ws.counts, nt, ws.item_shift, tile_blocks, ws.offs, ws.item_off, ws.items, ws.ctrl,
+                     bands_ev, ws.bits, ws.span, ws.hull);
   WCT_CHECK_LAUNCH();
   if (d.n > 0) {
-    hipLaunchKernelGGL((k_fill<T, TH, TW>), dim3(rblocks), dim3(256), 0, st, d, g, nsigma, ws.offs, ws.rank,
-                       ws.list);
+    const int fill_blocks = (int)((d.n + 255) / 256);
+    const int64_t split_blocks = nt < kSplitBlocks ? nt : kSplitBlocks;
+    hipLaunchKernelGGL((k_fill<T, TH, TW>), dim3((unsigned)(fill_blocks + split_blocks)), dim3(256), 0, st, d, g, nsigma,
+                       fill_blocks, ws.offs, ws.rank, ws.list, ws.counts, nt, ws.item_shift, grid);
     WCT_CHECK_LAUNCH();
   }
-  hipLaunchKernelGGL(k_items, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, ws.item_off, nt, ws.items);
-  WCT_CHECK_LAUNCH();
-  hipLaunchKernelGGL((k_zero_split<T, TH, TW>), dim3(1024), dim3(256), 0, st, g, ws.counts, nt, ws.item_shift,
-                     grid);
-  WCT_CHECK_LAUNCH();
+  hipError_t e = hipSuccess;
   if (prof) prof->end(st);
   static const char* const kTileName[3] = {"raster_tile_mean", "raster_tile_fluct", "raster_tile_normal"};
   if (prof) prof->begin(kTileName[mode], st);
@@ -641,7 +612,7 @@ hipError_t launch_raster_tiles(const DepoView<T>& d, const RasterGeom& g, double
   if (prof) prof->end(st);
   if (prof) prof->begin("raster_wide_rows", st);
 #define WCT_BIG_LAUNCH(M)                                                                                      \
-  hipLaunchKernelGGL((k_big<T, M>), dim3(256), dim3(256), 0, st, d, g, nsigma, seed, grid, ws.big, ws.ctrl, tables, \
+  hipLaunchKernelGGL((k_big<T, M>), dim3(256), dim3(256), 0, st, d, g, nsigma, seed, grid, ws.list, ws.ctrl, tables, \
                      lfact)
   if (mode == kModeBinomial)
     WCT_BIG_LAUNCH(kModeBinomial);

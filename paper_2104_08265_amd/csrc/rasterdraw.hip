@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(kDrawThreads, (draw_blocks<MODE, TH, TW>())) k
     if (!more_items && !more_zero) break;
     __syncthreads();  // every thread has read s_item
     if (more_items) {
-      const TileItem w_ = tile_item<TH, TW>(g, item, args.items, args.item_off, args.offs, args.item_shift);
+      const TileItem w_ = tile_item<TH, TW>(g, item, args.items, args.item_off, args.offs, counts, args.item_shift);
       const int tb0 = w_.tb0, tk0 = w_.tk0, th = w_.th, tw = w_.tw, r0 = w_.r0, r1 = w_.r1;
       const PlaneGeom& pl = g.pl[w_.plane];
       T* gp = grid + (int64_t)w_.ev * g.grid_ev_stride + pl.grid_off + (int64_t)tb0 * pl.nt + tk0;

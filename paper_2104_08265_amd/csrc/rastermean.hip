@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
     if (!more_items && !more_zero) break;
     __syncthreads();  // every thread has read s_item
     if (more_items) {
-      const TileItem w = tile_item<TH, TW>(g, item, items, item_off, offs, item_shift);
+      const TileItem w = tile_item<TH, TW>(g, item, items, item_off, offs, counts, item_shift);
       const PlaneGeom& pl = g.pl[w.plane];
       d4 acc[RB][CB];
 #pragma unroll

@@ -168,11 +168,12 @@ struct TileItem {
 template <int TH, int TW>
 __device__ __forceinline__ TileItem tile_item(const RasterGeom& g, int item, const int32_t* __restrict__ items,
                                               const int32_t* __restrict__ item_off,
-                                              const int32_t* __restrict__ offs, int item_shift) {
+                                              const int32_t* __restrict__ offs,
+                                              const int32_t* __restrict__ counts, int item_shift) {
   TileItem w;
   w.t = items[item];
-  const int chunk = item - item_off[w.t];
-  w.owned = (item_off[w.t + 1] - item_off[w.t]) == 1;
+  const int chunk = item - item_off[w.t], rows = counts[w.t];
+  w.owned = rows <= 1 << item_shift;
   w.ev = w.t / g.ntiles_ev;
   const int tin = w.t - w.ev * g.ntiles_ev;
   w.plane = find_plane(g, tin);
@@ -184,7 +185,7 @@ __device__ __forceinline__ TileItem tile_item(const RasterGeom& g, int item, con
   w.th = min(TH, pl.nb - w.tb0);
   w.tw = min(TW, pl.nt - w.tk0);
   w.r0 = offs[w.t] + (chunk << item_shift);
-  w.r1 = min(w.r0 + (1 << item_shift), offs[w.t + 1]);
+  w.r1 = w.r0 + min(1 << item_shift, rows - (chunk << item_shift));
   return w;
 }
 

@@ -242,79 +242,54 @@ hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, cons
 
 // One block per (event, tile): whether any impact row of the tile's wires, halo included,
 // holds a window (span hi != 0).
-__global__ void __launch_bounds__(256) k_wire_tiles(WireTileGeom g, const int2* __restrict__ span,
-                                                     uint8_t* __restrict__ live) {
-  const int ev = blockIdx.x / g.tiles_ev;
-  int t = blockIdx.x - ev * g.tiles_ev;
+// Whether rows [lo, hi) of a plane's row flags hold a set bit; rows lo + 32 first, lo + 32
+// (first + step), ... are looked at.
+__device__ __forceinline__ bool any_row(const uint32_t* __restrict__ bits, int lo, int hi, int first, int step) {
+  for (int wd = (lo >> 5) + first; wd <= (hi - 1) >> 5; wd += step) {
+    uint32_t v = bits[wd];
+    if (wd == lo >> 5) v &= ~0u << (lo & 31);
+    if (wd == (hi - 1) >> 5) v &= ~0u >> (31 - ((hi - 1) & 31));
+    if (v) return true;
+  }
+  return false;
+}
+
+// Latency: a few dependent loads per thread (from the row spans and in three launches, 44 us
+// on the three-plane detector).  The first n_events * tiles_ev blocks: one tile of the
+// direct pass each; the others: one (event, wire) per thread.
+__global__ void __launch_bounds__(256) k_reach(WireTileGeom g, int ntiles, int64_t nwires,
+                                               const uint32_t* __restrict__ bits, uint8_t* __restrict__ tiles,
+                                               uint8_t* __restrict__ wires) {
+  if ((int)blockIdx.x < ntiles) {
+    const int ev = blockIdx.x / g.tiles_ev;
+    int t = blockIdx.x - ev * g.tiles_ev;
+    int p = 0;
+    while (p + 1 < g.n_planes && t >= g.tile_off[p + 1]) ++p;
+    t -= g.tile_off[p];
+    const int wlo = max(0, t * kDirectWT - kDirectK), whi = min(g.nw[p], (t + 1) * kDirectWT + kDirectK);
+    const bool any = any_row(bits + (int64_t)ev * g.bits_ev + g.bit_off[p], wlo * g.I[p], whi * g.I[p], threadIdx.x, 256);
+    const bool live = __syncthreads_or(any) != 0;
+    if (threadIdx.x == 0) tiles[blockIdx.x] = live;
+    return;
+  }
+  const int64_t x = ((int64_t)blockIdx.x - ntiles) * 256 + threadIdx.x;
+  if (x >= nwires) return;
+  const int ev = (int)(x / g.wires_ev);
+  int w = (int)(x - (int64_t)ev * g.wires_ev);
   int p = 0;
-  while (p + 1 < g.n_planes && t >= g.tile_off[p + 1]) ++p;
-  t -= g.tile_off[p];
-  const int wlo = max(0, t * kDirectWT - kDirectK), whi = min(g.nw[p], (t + 1) * kDirectWT + kDirectK);
-  const int2* f = span + (int64_t)ev * g.rows_ev + g.row_off[p];
-  int any = 0;
-  for (int r = wlo * g.I[p] + (int)threadIdx.x; r < whi * g.I[p]; r += 256) any |= f[r].y != 0;
-  any = __syncthreads_or(any);
-  if (threadIdx.x == 0) live[blockIdx.x] = (uint8_t)(any != 0);
+  while (p + 1 < g.n_planes && w >= g.wire_off[p + 1]) ++p;
+  w -= g.wire_off[p];
+  const int wlo = max(0, w - g.K[p]), whi = min(g.nw[p], w + g.K[p] + 1);
+  wires[x] = any_row(bits + (int64_t)ev * g.bits_ev + g.bit_off[p], wlo * g.I[p], whi * g.I[p], 0, 1);
 }
 
-// One thread per (event, wire): whether any impact row of wires w - K .. w + K (inside
-// the plane) holds a window (span hi != 0).
-__global__ void __launch_bounds__(256) k_wire_live(WireTileGeom g, int64_t n, const int2* __restrict__ span,
-                                                    uint8_t* __restrict__ live) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
-    const int ev = (int)(x / g.wires_ev);
-    int w = (int)(x - (int64_t)ev * g.wires_ev);
-    int p = 0;
-    while (p + 1 < g.n_planes && w >= g.wire_off[p + 1]) ++p;
-    w -= g.wire_off[p];
-    const int wlo = max(0, w - g.K[p]), whi = min(g.nw[p], w + g.K[p] + 1);
-    const int2* f = span + (int64_t)ev * g.rows_ev + g.row_off[p];
-    int any = 0;
-    for (int r = wlo * g.I[p]; r < whi * g.I[p] && !any; ++r) any = f[r].y != 0;
-    live[x] = (uint8_t)any;
-  }
-}
-
-// One thread per (event, 32-row word): bit j set when row 32 word + j of the plane holds a
-// window (span hi != 0).
-__global__ void __launch_bounds__(256) k_row_bits(WireTileGeom g, int64_t n, const int2* __restrict__ span,
-                                                   uint32_t* __restrict__ bits) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
-    const int ev = (int)(x / g.bits_ev);
-    int wd = (int)(x - (int64_t)ev * g.bits_ev);
-    int p = 0;
-    while (p + 1 < g.n_planes && wd >= g.bit_off[p + 1]) ++p;
-    wd -= g.bit_off[p];
-    const int nb = g.nw[p] * g.I[p];
-    const int2* f = span + (int64_t)ev * g.rows_ev + g.row_off[p];
-    uint32_t v = 0;
-    for (int j = 0; j < 32; ++j) {
-      const int r = wd * 32 + j;
-      if (r < nb && f[r].y != 0) v |= 1u << j;
-    }
-    bits[x] = v;
-  }
-}
-
-hipError_t launch_row_bits(const WireTileGeom& g, int n_events, const int2* span, uint32_t* bits, hipStream_t st) {
-  const int64_t n = (int64_t)n_events * g.bits_ev;
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096;
-  hipLaunchKernelGGL(k_row_bits, dim3((unsigned)blocks), dim3(256), 0, st, g, n, span, bits);
-  return hipGetLastError();
-}
-
-hipError_t launch_wire_live(const WireTileGeom& g, int n_events, const int2* span, uint8_t* live, hipStream_t st) {
-  const int64_t n = (int64_t)n_events * g.wires_ev;
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096;
-  hipLaunchKernelGGL(k_wire_live, dim3((unsigned)blocks), dim3(256), 0, st, g, n, span, live);
-  return hipGetLastError();
-}
-
-hipError_t launch_wire_tiles(const WireTileGeom& g, int n_events, const int2* span, uint8_t* live, hipStream_t st) {
-  if (n_events <= 0 || g.tiles_ev <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_wire_tiles, dim3((unsigned)(n_events * g.tiles_ev)), dim3(256), 0, st, g, span, live);
+hipError_t launch_reach(const WireTileGeom& g, int n_events, const uint32_t* bits, uint8_t* tiles, uint8_t* wires,
+                        hipStream_t st) {
+  const int64_t ntiles = (int64_t)n_events * g.tiles_ev, nwires = (int64_t)n_events * g.wires_ev;
+  const int64_t blocks = ntiles + (nwires + 255) / 256;
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_reach, dim3((unsigned)blocks), dim3(256), 0, st, g, (int)ntiles, nwires, bits, tiles, wires);
   return hipGetLastError();
 }
 
