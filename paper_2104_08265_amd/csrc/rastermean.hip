@@ -39,10 +39,12 @@ constexpr int mean_blocks(int th, int tw) { return th * tw > 6144 ? 2 : (th * tw
 // upper edge from the next lane, the last one from the next block's first.  Edges are
 // clipped to the window, so they coincide outside it and the weights there are 0.  Both
 // axes go through one loop, with one erf in it: its coefficients are then live once.
+// Edges beyond the polynomial (windows past 4.2 sigma, or widths next to the rounding of the
+// position, whose edges round to several sigma) take the library's erf of the quotient.
 struct AxisWin {
-  double lo, hi, mu, inv;  // window, centre, 1 / (sqrt 2 sigma)
+  double lo, hi, mu, s2, inv;  // window, centre, sqrt 2 sigma, 1 / (sqrt 2 sigma)
 };
-template <bool POLY>
+__device__ __attribute__((noinline)) double erf_call(double x) { return erf(x); }
 __device__ __forceinline__ void stage_group(double* __restrict__ da, double* __restrict__ db, int a0, int a1, int b0,
                                             int b1, int ca, int cb, AxisWin u, AxisWin t, double q, int l16) {
   const int na = a1 - a0 + 2, n = na + (b1 - b0 + 2);  // blocks of edges: one more than blocks of cells
@@ -51,9 +53,13 @@ __device__ __forceinline__ void stage_group(double* __restrict__ da, double* __r
     const bool second = i >= na;  // uniform
     const int blk = second ? b0 + (i - na) : a0 + i;
     const double c = (double)((second ? cb : ca) + 16 * blk + l16);
-    const double x = (fmin(fmax(c, second ? t.lo : u.lo), second ? t.hi : u.hi) - (second ? t.mu : u.mu)) *
-                     (second ? t.inv : u.inv);
-    const double v = POLY ? erf_poly(x) : erf(x);
+    const double d = fmin(fmax(c, second ? t.lo : u.lo), second ? t.hi : u.hi) - (second ? t.mu : u.mu);
+    const double x = d * (second ? t.inv : u.inv);
+    double v;
+    if (wave_any(!(fabs(x) <= kErfPolyEdge)))
+      v = erf_call(d / (second ? t.s2 : u.s2));
+    else
+      v = erf_poly(x);
     const double up = __shfl(l16 == 0 ? v : e, (l16 + 1) & 15, 16);  // lane 15 reads lane 0's next block
     if (i != 0 && i != na) (second ? db : da)[16 * (blk - 1) + l16] = (second ? 0.5 : q * 0.5) * (up - e);
     e = v;
@@ -65,7 +71,7 @@ __device__ __forceinline__ void stage_group(double* __restrict__ da, double* __r
 // A block takes work items and clearing groups in step, as the fluctuated tile kernel
 // does.  Wave v owns the tile's 16-row blocks v, v + 4, ... (interleaved, so that a window
 // of 61 rows occupies all four waves) over all its 16-tick blocks.
-template <typename T, int TH, int TW, bool POLY>
+template <typename T, int TH, int TW>
 __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView<T> d, RasterGeom g, double nsigma, T* __restrict__ grid,
                                                       const int32_t* __restrict__ list,
                                                       const int32_t* __restrict__ offs,
@@ -105,7 +111,7 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
         // wave v stages the group of rows rc + 4 v .. + 3, sixteen lanes per row
         const int slot = 4 * wv + sub, r = rc + slot;
         double q = 0.0;
-        AxisWin u{0.0, 0.0, 0.0, 1.0}, t{0.0, 0.0, 0.0, 1.0};
+        AxisWin u{0.0, 0.0, 0.0, 1.0, 1.0}, t{0.0, 0.0, 0.0, 1.0, 1.0};
         int a0 = TH / 16, a1 = -1, b0 = TW / 16, b1 = -1;
         if (r < w.r1) {
           const RowWin rw = row_window(d, (int64_t)list[r], g, nsigma);
@@ -113,8 +119,8 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
           const int kk0 = max(rw.k0, w.tk0), kk1 = min(rw.k1, w.tk0 + w.tw);
           if (rw.ok && bb0 < bb1 && kk0 < kk1) {
             q = rw.q;
-            u = AxisWin{rw.ulo, rw.uhi, rw.u, 1.0 / (rw.su * kSqrt2)};
-            t = AxisWin{rw.tlo, rw.thi, rw.t, 1.0 / (rw.st * kSqrt2)};
+            u = AxisWin{rw.ulo, rw.uhi, rw.u, rw.su * kSqrt2, 1.0 / (rw.su * kSqrt2)};
+            t = AxisWin{rw.tlo, rw.thi, rw.t, rw.st * kSqrt2, 1.0 / (rw.st * kSqrt2)};
             a0 = (bb0 - w.tb0) >> 4;
             a1 = (bb1 - 1 - w.tb0) >> 4;
             b0 = (kk0 - w.tk0) >> 4;
@@ -133,7 +139,7 @@ __global__ void __launch_bounds__(256, mean_blocks(TH, TW)) k_tile_mean(DepoView
         b0 = __builtin_amdgcn_readfirstlane(b0);
         b1 = __builtin_amdgcn_readfirstlane(b1);
         if (a0 <= a1)
-          stage_group<POLY>(s_a + slot * SA, s_b + slot * SB, a0, a1, b0, b1, w.tb0, w.tk0, u, t, q, l16);
+          stage_group(s_a + slot * SA, s_b + slot * SB, a0, a1, b0, b1, w.tb0, w.tk0, u, t, q, l16);
         if (lane == 0) s_rng[wv] = make_int4(a0, a1, b0, b1);
         __syncthreads();
 #pragma unroll
@@ -188,15 +194,8 @@ template <typename T, int TH, int TW>
 hipError_t launch_tile_mean(const DepoView<T>& d, const RasterGeom& g, double nsigma, T* grid, const RasterWs& ws,
                             int n_cu, hipStream_t st) {
   const dim3 blocks((unsigned)(n_cu * mean_blocks(TH, TW)));
-#define WCT_MEAN_LAUNCH(POLY)                                                                                       \
-  hipLaunchKernelGGL((k_tile_mean<T, TH, TW, POLY>), blocks, dim3(256), 0, st, d, g, nsigma, grid, ws.list, ws.offs, \
-                     ws.items, ws.item_off, ws.counts, ws.ntiles, ws.item_shift, ws.ctrl, ws.hull)
-  // the polynomial wherever its range holds the windows' edges, else the library's erf
-  if (nsigma <= kErfPolyNsigma)
-    WCT_MEAN_LAUNCH(true);
-  else
-    WCT_MEAN_LAUNCH(false);
-#undef WCT_MEAN_LAUNCH
+  hipLaunchKernelGGL((k_tile_mean<T, TH, TW>), blocks, dim3(256), 0, st, d, g, nsigma, grid, ws.list, ws.offs, ws.items,
+                     ws.item_off, ws.counts, ws.ntiles, ws.item_shift, ws.ctrl, ws.hull);
   return hipGetLastError();
 }
 
