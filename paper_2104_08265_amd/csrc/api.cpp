@@ -460,6 +460,8 @@ int run_convolve(wct_plan* P, const T* grid, int n_events, T* wave, Carver& cv, 
       wt.live = tiles + tg.tile_off[p];
       wt.ev_stride = tg.tiles_ev;
       wt.ntile = tg.tile_off[p + 1] - tg.tile_off[p];
+      // without noise pass C reads no wire that no window reaches (WireLive)
+      wt.skip_dead = !(noise && noise->noise && P->noise_amp[p]);
       if (G.I <= 10) {
         wt.rowbits = rbits + tg.bit_off[p];
         wt.bits_ev = tg.bits_ev;

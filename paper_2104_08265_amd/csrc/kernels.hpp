@@ -177,13 +177,14 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // rows themselves (one bit each), as wct_simulate records them: a tile no row reaches
 // writes a zero M^ without reading S^, a live tile takes the rows no window reached as
 // zeros without reading them, so pass A writes no spectrum for a row pair no window reached.
-constexpr int kDirectTileWires = 512, kDirectHalfWires = 10;
+constexpr int kDirectTileWires = 256, kDirectHalfWires = 10;
 struct WireTiles {
   const uint8_t* live = nullptr;  // [event][tile] of this plane (ev_stride apart); nullptr: all
   int64_t ev_stride = 0;
   int ntile = 0;
   const uint32_t* rowbits = nullptr;  // [event][bits_ev words] from this plane's first word:
   int64_t bits_ev = 0;                // bit r of the plane set when row r holds a window
+  bool skip_dead = false;  // nothing reads the spectrum of a tile that no row reaches: it is not written
 };
 // Wires whose output some window reaches (a row of wires w - K .. w + K holds one), as
 // wct_simulate records them: the inverse row transform writes the zero waveform of any

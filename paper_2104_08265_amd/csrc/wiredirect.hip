@@ -21,7 +21,10 @@ namespace {
 constexpr int kDirectK = kDirectHalfWires;  // response half-width the kernel is compiled for
 constexpr int kDirectWL = 8;                // output wires per lane
 constexpr int kDirectWT = 64 * kDirectWL;   // output wires per block
-static_assert(kDirectWT == kDirectTileWires, "tile flags and blocks share their wires");
+constexpr int kDirectSubs = kDirectWT / kDirectTileWires;  // tiles of the flags per block
+constexpr int kSubLanes = 64 / kDirectSubs;
+constexpr int kSubSpan = kDirectTileWires + 2 * kDirectK;           // S^ wires staged per phase and tile
+constexpr int kSubPstr = kSubSpan + kSubSpan / kDirectWL + 1;       // with the pads below
 constexpr int kDirectSpan = kDirectWT + 2 * kDirectK;  // S^ wires staged per phase
 // LDS stride of one frequency's staged wires: one pad element every kDirectWL wires, so
 // that lanes reading wires kDirectWL apart hit distinct banks
@@ -30,51 +33,81 @@ constexpr int kDirectPstr = kDirectSpan + kDirectSpan / kDirectWL + 1;
 }  // namespace
 
 // One block: kChunk tick frequencies (one per wave, so a wave's coefficients are
-// uniform: scalar loads) x kDirectWT consecutive wires of one (chunk, event).  Phases are
-// staged through LDS in two buffers: the next phase's global loads are in flight while
-// the current one is summed.
+// uniform: scalar loads) x two tiles of kDirectTileWires wires of one (chunk, event).  Phases
+// are staged through LDS in two buffers: the next phase's global loads are in flight while
+// the current one is summed.  With tile flags the blocks take the tiles that some row
+// reaches, two by two, whatever lies between them, and the last blocks the others: bound by
+// its multiply-adds, the pass costs what the reached tiles do (16 sparse events, 41% of the
+// 256-wire tiles reached: 10.6 -> 8.5 ms; in whole 512-wire blocks, 51%).
 template <typename T>
 __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __restrict__ shat, int64_t shat_ev_stride,
                                                                const cx<T>* __restrict__ rtick, cx<T>* __restrict__ mhat,
                                                                int64_t mhat_ev_stride, int nw, int nphase, int nchunk,
                                                                int ntile, int n_events, WireTiles wt) {
-  constexpr int K = kDirectK, NK = 2 * K + 1, WL = kDirectWL, WT = kDirectWT;
-  constexpr int SPAN = kDirectSpan, PSTR = kDirectPstr, C = kChunk;
+  constexpr int K = kDirectK, NK = 2 * K + 1, WL = kDirectWL;
+  constexpr int SUBS = kDirectSubs, SW = kDirectTileWires, SPAN = kSubSpan, PSTR = SUBS * kSubPstr, C = kChunk;
   constexpr int CPV = 16 / (int)sizeof(cx<T>);  // complex values per 16-byte load
   constexpr int VPW = C / CPV;                  // 16-byte loads per staged wire
-  constexpr int NE = SPAN * VPW, NPT = (NE + 64 * C - 1) / (64 * C);
+  constexpr int NE = SUBS * SPAN * VPW, NPT = (NE + 64 * C - 1) / (64 * C);
   using V = typename Vec16<T>::type;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);  // [2][C][PSTR]
   const int L = xcd_remap(blockIdx.x, gridDim.x);
   const int tile = L % ntile, rest = L / ntile;
   const int ev = rest % n_events, ch = rest / n_events;
-  const int w0 = tile * WT;
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int f = __builtin_amdgcn_readfirstlane(tid >> 6);  // this wave's frequency in the chunk
-  if (wt.live && !wt.live[ev * wt.ev_stride + tile]) {  // no row reaches the tile: M^ = 0
+  // the block's tiles: the reached ones come first, then the others, each in order
+  const int nsub = (nw + SW - 1) / SW;
+  int sub[SUBS];
+  bool dead = false;
+#pragma unroll
+  for (int b = 0; b < SUBS; ++b) sub[b] = SUBS * tile + b;
+  if (wt.live && nsub <= 64) {
+    const bool live = lane < nsub && wt.live[ev * wt.ev_stride + lane];
+    const uint64_t m = __ballot(live), below = (1ull << lane) - 1ull;
+    const int nlive = __popcll(m);
+    const int place = lane >= nsub ? -1 : live ? __popcll(m & below) : nlive + lane - __popcll(m & below);
+    dead = SUBS * tile >= nlive;
+#pragma unroll
+    for (int b = 0; b < SUBS; ++b) {
+      const uint64_t who = __ballot(place == SUBS * tile + b);
+      sub[b] = who ? __builtin_ctzll(who) : nsub;
+    }
+  }
+  // first wire of each tile (past the grid, halo included, where there is none)
+  int w0s[SUBS];
+#pragma unroll
+  for (int b = 0; b < SUBS; ++b) w0s[b] = sub[b] < nsub ? sub[b] * SW : nw + K;
+  const int lsub = lane / kSubLanes, w_lane = (lsub == 0 ? w0s[0] : w0s[SUBS - 1]) + WL * (lane % kSubLanes);
+  static_assert(SUBS == 2, "a lane's tile is the first or the last");
+  if (dead) {  // no row reaches the tiles: M^ = 0
+    if (wt.skip_dead) return;
     cx<T>* dst = mhat + ev * mhat_ev_stride;
     for (int o = 0; o < WL; ++o) {
-      const int w = w0 + WL * lane + o;
+      const int w = w_lane + o;
       if (w < nw) dst[(int64_t)w * (nchunk * C) + ch * C + f] = mk(T(0), T(0));
     }
     return;
   }
   const cx<T>* src = shat + ev * shat_ev_stride + (int64_t)ch * nphase * nw * C;
-  // the row flags of the staged wires (rows of wires w0 - K .. w0 + WT + K), one bit each
+  // the row flags of the staged wires (rows of wires w0 - K .. w0 + SW + K), one bit each
   constexpr int kBitWords = (SPAN * 10 + 31) / 32 + 2;  // up to 10 phases
-  __shared__ uint32_t s_bits[kBitWords];
-  const int r_lo = max(0, w0 - K) * nphase, wd0 = r_lo >> 5;
+  __shared__ uint32_t s_bits[SUBS * kBitWords];
   const bool bits = wt.rowbits != nullptr && nphase <= 10;
+  auto first_word = [&](int b) { return max(0, w0s[b] - K) * nphase >> 5; };
   if (bits) {
-    const int r_hi = min(nw, w0 + WT + K) * nphase, wd1 = (r_hi + 31) >> 5;
-    for (int x = tid; x < wd1 - wd0; x += 64 * C) s_bits[x] = wt.rowbits[ev * wt.bits_ev + wd0 + x];
+#pragma unroll
+    for (int b = 0; b < SUBS; ++b) {
+      const int wd0 = first_word(b), wd1 = (min(nw, w0s[b] + SW + K) * nphase + 31) >> 5;
+      for (int x = tid; x < wd1 - wd0; x += 64 * C) s_bits[b * kBitWords + x] = wt.rowbits[ev * wt.bits_ev + wd0 + x];
+    }
     __syncthreads();
   }
-  auto row_live = [&](int w, int i) {
+  auto row_live = [&](int b, int w, int i) {
     if (!bits) return true;
     const int r = w * nphase + i;
-    return ((s_bits[(r >> 5) - wd0] >> (r & 31)) & 1u) != 0;
+    return ((s_bits[b * kBitWords + (r >> 5) - (b == 0 ? first_word(0) : first_word(SUBS - 1))] >> (r & 31)) & 1u) != 0;
   };
 
   V stage[NPT];
@@ -83,9 +116,9 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
 #pragma unroll
     for (int u = 0; u < NPT; ++u) {
       const int e = tid + u * 64 * C;
-      const int w = w0 - K + e / VPW;
+      const int b = e / (SPAN * VPW), w = (b == 0 ? w0s[0] : w0s[SUBS - 1]) - K + e / VPW - b * SPAN;
       V v = {};
-      if (e < NE && w >= 0 && w < nw && row_live(w, i)) v = *reinterpret_cast<const V*>(s + (int64_t)w * C + (e % VPW) * CPV);
+      if (e < NE && w >= 0 && w < nw && row_live(b, w, i)) v = *reinterpret_cast<const V*>(s + (int64_t)w * C + (e % VPW) * CPV);
       stage[u] = v;
     }
   };
@@ -95,9 +128,10 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
     for (int u = 0; u < NPT; ++u) {
       const int e = tid + u * 64 * C;
       if (e < NE) {
-        const int x = e / VPW, f0 = (e % VPW) * CPV;
+        const int b = e / (SPAN * VPW), x = e / VPW - b * SPAN, f0 = (e % VPW) * CPV;
 #pragma unroll
-        for (int q = 0; q < CPV; ++q) d[(f0 + q) * PSTR + x + x / WL] = mk(stage[u][2 * q], stage[u][2 * q + 1]);
+        for (int q = 0; q < CPV; ++q)
+          d[(f0 + q) * PSTR + b * kSubPstr + x + x / WL] = mk(stage[u][2 * q], stage[u][2 * q + 1]);
       }
     }
   };
@@ -114,14 +148,14 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
     cx<T> r[NK];
 #pragma unroll
     for (int k = 0; k < NK; ++k) r[k] = coef[k];
-    // staged wire x = WL lane + j (j < WL + 2K) sits at (WL + 1) lane + j + j / WL
-    const cx<T>* s = lds + (i & 1) * C * PSTR + f * PSTR + (WL + 1) * lane;
+    // a tile's staged wire x = WL l + j (lane l of the tile, j < WL + 2K) sits at (WL + 1) l + j + j / WL
+    const cx<T>* s = lds + (i & 1) * C * PSTR + f * PSTR + lsub * kSubPstr + (WL + 1) * (lane % kSubLanes);
 #pragma unroll
     for (int j = 0; j < WL + 2 * K; ++j) {
       const cx<T> v = s[j + j / WL];
 #pragma unroll
       for (int o = 0; o < WL; ++o) {
-        if (j - o < 0 || j - o > 2 * K) continue;  // output wire w0 + WL lane + o, tap k = j - o - K
+        if (j - o < 0 || j - o > 2 * K) continue;  // output wire w_lane + o, tap k = j - o - K
         const cx<T> c = r[j - o];
         ax[o] = fma(c.x, v.x, ax[o]);
         ax[o] = fma(-c.y, v.y, ax[o]);
@@ -136,7 +170,7 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
   const int fpad = nchunk * C;
 #pragma unroll
   for (int o = 0; o < WL; ++o) {
-    const int w = w0 + WL * lane + o;
+    const int w = w_lane + o;
     if (w < nw) dst[(int64_t)w * fpad + ch * C + f] = mk(ax[o], ay[o]);  // [w][fpad]
   }
 }
@@ -208,7 +242,7 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_adj_direct(const cx<T>*
 namespace {
 template <typename T>
 size_t direct_lds() {
-  return sizeof(cx<T>) * 2 * kChunk * kDirectPstr;
+  return sizeof(cx<T>) * 2 * kChunk * kDirectSubs * kSubPstr;
 }
 }  // namespace
 
@@ -230,7 +264,7 @@ hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, cons
                                  int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, hipStream_t st,
                                  const WireTiles& wt) {
   static_assert(kChunk == 4, "one wave per frequency of a chunk");
-  const int ntile = (nw + kDirectWT - 1) / kDirectWT;
+  const int ntile = (nw + kDirectWT - 1) / kDirectWT;  // pairs of tiles
   const int64_t nblk = (int64_t)nchunk * n_events * ntile;
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x7fffffff) return hipErrorInvalidValue;
@@ -266,7 +300,8 @@ __global__ void __launch_bounds__(256) k_reach(WireTileGeom g, int ntiles, int64
     int p = 0;
     while (p + 1 < g.n_planes && t >= g.tile_off[p + 1]) ++p;
     t -= g.tile_off[p];
-    const int wlo = max(0, t * kDirectWT - kDirectK), whi = min(g.nw[p], (t + 1) * kDirectWT + kDirectK);
+    const int wlo = max(0, t * kDirectTileWires - kDirectK);
+    const int whi = min(g.nw[p], (t + 1) * kDirectTileWires + kDirectK);
     const bool any = any_row(bits + (int64_t)ev * g.bits_ev + g.bit_off[p], wlo * g.I[p], whi * g.I[p], threadIdx.x, 256);
     const bool live = __syncthreads_or(any) != 0;
     if (threadIdx.x == 0) tiles[blockIdx.x] = live;
@@ -301,7 +336,7 @@ hipError_t launch_colpass_adj_direct(const cx<T>* ghat, int64_t ghat_ev_stride, 
   const int64_t nblk = (int64_t)nchunk * n_events * ntile;
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x7fffffff) return hipErrorInvalidValue;
-  const size_t lds = direct_lds<T>() / 2;  // one buffer
+  const size_t lds = sizeof(cx<T>) * kChunk * kDirectPstr;
   hipLaunchKernelGGL((k_colpass_adj_direct<T>), dim3((unsigned)nblk), dim3(64 * kChunk), lds, st, ghat,
                      ghat_ev_stride, rtick, hhat, hhat_ev_stride, nw, nphase, nchunk, ntile, n_events);
   return hipGetLastError();
