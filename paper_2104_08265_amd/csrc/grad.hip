@@ -49,6 +49,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // The factors of cells c0 .. c0 + n - 1 of an axis.  A lane evaluates one edge and takes the
 // upper one of its cell from the next lane, 63 cells a pass.  Edges outside the window are
 // clipped to it (their z is then fixed, so they carry no derivative).
+template <typename T>
 __device__ __forceinline__ void axis_factors(int c0, int n, double mu, double sigma, double lo, double hi,
                                              AxisD* __restrict__ out, int lane) {
   constexpr double inv_sqrt2pi = 0.39894228040143267794, sqrt_half = 0.70710678118654752440;
@@ -62,7 +63,7 @@ __device__ __forceinline__ void axis_factors(int c0, int n, double mu, double si
     // beyond the polynomial (wide windows, or widths next to the rounding of the position)
     const bool wide = !(fabs(z) * sqrt_half <= kErfPolyEdge);
     double e;
-    if (__ballot(wide)) {
+    if (sizeof(T) == 8 || __ballot(wide)) {  // FP64 plans: the polynomial's error would show
       z = d / sigma;
       e = erf_call(z * sqrt_half);
     } else {
@@ -127,10 +128,10 @@ __global__ void __launch_bounds__(256, 4) k_grad_gather(DepoView<T> d, RasterGeo
       const int lt = lane & (width - 1), lr = lane / width;
       for (int cb = b0; cb < b1; cb += kGradRows) {
         const int nbr = min(kGradRows, b1 - cb);
-        axis_factors(cb, nbr, u, su, ulo, uhi, s_a[wv], lane);
+        axis_factors<T>(cb, nbr, u, su, ulo, uhi, s_a[wv], lane);
         for (int ck = k0; ck < k1; ck += width * kGradTicks) {
           const int nkr = min(width * kGradTicks, k1 - ck);
-          axis_factors(ck, nkr, t, st, tlo, thi, s_b[wv], lane);
+          axis_factors<T>(ck, nkr, t, st, tlo, thi, s_b[wv], lane);
           wave_fence();
           AxisD B[kGradTicks];
           bool in[kGradTicks];

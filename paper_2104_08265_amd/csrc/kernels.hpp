@@ -41,12 +41,13 @@ constexpr int kQueues = 8, kQueueStride = 32;  // one queue per XCD, each head o
 constexpr int kItemShiftMin = 4, kItemShiftMax = 8;
 constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kernels at most
 
-// Raster tile variants: X(real type, TH rows, TW ticks, tile-kernel blocks per CU).
+// Raster tile variants: X(real type, TH rows, TW ticks, blocks per CU: part of a variant's name
+// in the tuner's cache; the tile kernels take what their LDS and registers admit).
 // Tall tiles: a window of up to 129 impact rows (sigma_p <= 2 pitches at 3 sigma) spans
 // at most 2 tile rows, so typical rows take the tile path.  TW is even (the tick pairs that
 // share a Philox block never straddle two tiles) and a multiple of 16 bytes (tiles are
-// cleared with 16-byte stores); TH * TW <= 2^13 (tile offsets beside the packed electron
-// count of the chop-down queue).  Smaller tiles take less LDS, so more blocks share a CU,
+// cleared with 16-byte stores); TH * TW <= 2^13 (tile offsets beside the uniform in a
+// waiting cell's entry).  Smaller tiles take less LDS, so more blocks share a CU,
 // but more rows straddle tiles.  The first variant of a type is a plan's default; the
 // raster tuner (wct_plan_tune_raster) times them on an event's rows.
 #define WCT_TILE_VARIANTS(X) \

@@ -38,7 +38,7 @@ constexpr int kDirectPstr = kDirectSpan + kDirectSpan / kDirectWL + 1;
 // the current one is summed.  With tile flags the blocks take the tiles that some row
 // reaches, two by two, whatever lies between them, and the last blocks the others: bound by
 // its multiply-adds, the pass costs what the reached tiles do (16 sparse events, 41% of the
-// 256-wire tiles reached: 10.6 -> 8.5 ms; in whole 512-wire blocks, 51%).
+// 256-wire tiles reached: 10.6 -> 7.8 ms; in whole 512-wire blocks, 51%).
 template <typename T>
 __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __restrict__ shat, int64_t shat_ev_stride,
                                                                const cx<T>* __restrict__ rtick, cx<T>* __restrict__ mhat,
