@@ -55,9 +55,11 @@ COUNTERS_JSON = os.path.join(PROFILES, "raster_counters.json")
 def family(kernel_name):
     """Kernel family (the names of the per-kernel table) of a device kernel symbol."""
     n = kernel_name.split("(")[0]
-    if "k_tile<" in n:  # k_tile<T, mode, ...>: 0 mean, 1 binomial, 2 normal approximation
+    if "k_tile_mean<" in n:
+        return "raster_tile_mean"
+    if "k_tile<" in n:  # k_tile<T, mode, ...>: 1 binomial, 2 normal approximation
         mode = n.split("k_tile<", 1)[1].split(",")[1].strip()
-        return {"0": "raster_tile_mean", "1": "raster_tile_fluct", "2": "raster_tile_normal"}.get(mode)
+        return {"1": "raster_tile_fluct", "2": "raster_tile_normal"}.get(mode)
     if "k_big<" in n:
         return "raster_wide_rows"
     if "k_rows_r2c" in n:
