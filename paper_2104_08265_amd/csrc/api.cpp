@@ -474,7 +474,8 @@ int run_convolve(wct_plan* P, const T* grid, int n_events, T* wave, Carver& cv, 
     if (P->wire_direct[p])
       PROF_LAUNCH(P, "colpass", st,
                   launch_colpass_direct<T>(shat + G.shat_off, P->shat_elems, static_cast<const cx<T>*>(P->rtick[p]),
-                                           mhat + G.mhat_off, P->mhat_elems, G.nw, G.I, G.nchunk, n_events, st, wt),
+                                           mhat + G.mhat_off, P->mhat_elems, G.nw, G.I, G.nchunk, n_events, P->n_cu,
+                                           st, wt),
                   "column pass launch");
     else
       PROF_LAUNCH(P, "colpass", st,
@@ -524,7 +525,7 @@ int run_backward(wct_plan* P, const wct_depos* d, const wct_opts* o, const T* gw
       PROF_LAUNCH(P, "adj_colpass", st,
                   launch_colpass_adj_direct<T>(ghat + G.mhat_off, P->mhat_elems,
                                                static_cast<const cx<T>*>(P->rtick[p]), hhat + G.shat_off,
-                                               P->shat_elems, G.nw, G.I, G.nchunk, ne, st),
+                                               P->shat_elems, G.nw, G.I, G.nchunk, ne, P->n_cu, st),
                   "adjoint column pass launch");
     else
       PROF_LAUNCH(P, "adj_colpass", st,

@@ -214,8 +214,8 @@ void wiredirect_init_kernels();
 // wt (optional): the plane's tile flags; a tile no row reaches writes zeros.
 template <typename T>
 hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, const cx<T>* rtick, cx<T>* mhat,
-                                 int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, hipStream_t st,
-                                 const WireTiles& wt = WireTiles());
+                                 int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, int n_cu,
+                                 hipStream_t st, const WireTiles& wt = WireTiles());
 // From the row flags: the direct pass's tile flags of every plane and event (plane p's
 // tiles start at tile_off[p] of an event's tiles_ev),
 struct WireTileGeom {
@@ -231,7 +231,7 @@ hipError_t launch_reach(const WireTileGeom& g, int n_events, const uint32_t* bit
                         hipStream_t st);
 template <typename T>
 hipError_t launch_colpass_adj_direct(const cx<T>* ghat, int64_t ghat_ev_stride, const cx<T>* rtick, cx<T>* hhat,
-                                     int64_t hhat_ev_stride, int nw, int nphase, int nchunk, int n_events,
+                                     int64_t hhat_ev_stride, int nw, int nphase, int nchunk, int n_events, int n_cu,
                                      hipStream_t st);
 template <typename T>
 hipError_t launch_colpass_adj(const cx<T>* ghat, int64_t ghat_ev_stride, const cx<T>* rtil, cx<T>* hhat,

@@ -19,16 +19,22 @@ namespace wct {
 namespace {
 
 constexpr int kDirectK = kDirectHalfWires;  // response half-width the kernel is compiled for
-constexpr int kDirectWL = 8;                // output wires per lane
-constexpr int kDirectWT = 64 * kDirectWL;   // output wires per block
-constexpr int kDirectSubs = kDirectWT / kDirectTileWires;  // tiles of the flags per block
-constexpr int kSubLanes = 64 / kDirectSubs;
-constexpr int kSubSpan = kDirectTileWires + 2 * kDirectK;           // S^ wires staged per phase and tile
-constexpr int kSubPstr = kSubSpan + kSubSpan / kDirectWL + 1;       // with the pads below
-constexpr int kDirectSpan = kDirectWT + 2 * kDirectK;  // S^ wires staged per phase
-// LDS stride of one frequency's staged wires: one pad element every kDirectWL wires, so
-// that lanes reading wires kDirectWL apart hit distinct banks
-constexpr int kDirectPstr = kDirectSpan + kDirectSpan / kDirectWL + 1;
+// WL output wires per lane, 64 WL per block: eight, or four on small launches (direct_lanes).
+// A block's ten phases run one after the other, so a launch that cannot fill the chip takes
+// a block's time, and halving the block's wires halves it; eight read fewer staged values per
+// multiply-add.
+template <int WL>
+struct DirectTile {
+  static constexpr int WT = 64 * WL;                      // output wires per block
+  static constexpr int SUBS = WT / kDirectTileWires;      // tiles of the flags per block
+  static constexpr int SUB_LANES = 64 / SUBS;
+  static constexpr int SUB_SPAN = kDirectTileWires + 2 * kDirectK;  // S^ wires staged per phase and tile
+  // LDS stride of one frequency's staged wires of a tile, and of a block's contiguous wires: one
+  // pad element every WL wires, so that lanes reading wires WL apart hit distinct banks
+  static constexpr int SUB_PSTR = SUB_SPAN + SUB_SPAN / WL + 1;
+  static constexpr int SPAN = WT + 2 * kDirectK;
+  static constexpr int PSTR = SPAN + SPAN / WL + 1;
+};
 
 }  // namespace
 
@@ -39,13 +45,14 @@ constexpr int kDirectPstr = kDirectSpan + kDirectSpan / kDirectWL + 1;
 // reaches, two by two, whatever lies between them, and the last blocks the others: bound by
 // its multiply-adds, the pass costs what the reached tiles do (16 sparse events, 41% of the
 // 256-wire tiles reached: 10.6 -> 7.8 ms; in whole 512-wire blocks, 51%).
-template <typename T>
+template <typename T, int WL>
 __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __restrict__ shat, int64_t shat_ev_stride,
                                                                const cx<T>* __restrict__ rtick, cx<T>* __restrict__ mhat,
                                                                int64_t mhat_ev_stride, int nw, int nphase, int nchunk,
                                                                int ntile, int n_events, WireTiles wt) {
-  constexpr int K = kDirectK, NK = 2 * K + 1, WL = kDirectWL;
-  constexpr int SUBS = kDirectSubs, SW = kDirectTileWires, SPAN = kSubSpan, PSTR = SUBS * kSubPstr, C = kChunk;
+  using D = DirectTile<WL>;
+  constexpr int K = kDirectK, NK = 2 * K + 1, SUBS = D::SUBS, SW = kDirectTileWires;
+  constexpr int SPAN = D::SUB_SPAN, SUB_PSTR = D::SUB_PSTR, SUB_LANES = D::SUB_LANES, PSTR = SUBS * SUB_PSTR, C = kChunk;
   constexpr int CPV = 16 / (int)sizeof(cx<T>);  // complex values per 16-byte load
   constexpr int VPW = C / CPV;                  // 16-byte loads per staged wire
   constexpr int NE = SUBS * SPAN * VPW, NPT = (NE + 64 * C - 1) / (64 * C);
@@ -79,8 +86,8 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
   int w0s[SUBS];
 #pragma unroll
   for (int b = 0; b < SUBS; ++b) w0s[b] = sub[b] < nsub ? sub[b] * SW : nw + K;
-  const int lsub = lane / kSubLanes, w_lane = (lsub == 0 ? w0s[0] : w0s[SUBS - 1]) + WL * (lane % kSubLanes);
-  static_assert(SUBS == 2, "a lane's tile is the first or the last");
+  const int lsub = lane / SUB_LANES, w_lane = (lsub == 0 ? w0s[0] : w0s[SUBS - 1]) + WL * (lane % SUB_LANES);
+  static_assert(SUBS <= 2, "a lane's tile is the first or the last");
   if (dead) {  // no row reaches the tiles: M^ = 0
     if (wt.skip_dead) return;
     cx<T>* dst = mhat + ev * mhat_ev_stride;
@@ -131,7 +138,7 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
         const int b = e / (SPAN * VPW), x = e / VPW - b * SPAN, f0 = (e % VPW) * CPV;
 #pragma unroll
         for (int q = 0; q < CPV; ++q)
-          d[(f0 + q) * PSTR + b * kSubPstr + x + x / WL] = mk(stage[u][2 * q], stage[u][2 * q + 1]);
+          d[(f0 + q) * PSTR + b * SUB_PSTR + x + x / WL] = mk(stage[u][2 * q], stage[u][2 * q + 1]);
       }
     }
   };
@@ -149,7 +156,7 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
 #pragma unroll
     for (int k = 0; k < NK; ++k) r[k] = coef[k];
     // a tile's staged wire x = WL l + j (lane l of the tile, j < WL + 2K) sits at (WL + 1) l + j + j / WL
-    const cx<T>* s = lds + (i & 1) * C * PSTR + f * PSTR + lsub * kSubPstr + (WL + 1) * (lane % kSubLanes);
+    const cx<T>* s = lds + (i & 1) * C * PSTR + f * PSTR + lsub * SUB_PSTR + (WL + 1) * (lane % SUB_LANES);
 #pragma unroll
     for (int j = 0; j < WL + 2 * K; ++j) {
       const cx<T> v = s[j + j / WL];
@@ -179,15 +186,15 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
 // (the correlation's transpose; G^ rows outside the wires are zero).  One staged window
 // of G^ serves all I phases: each lane keeps its 8 + 2K values in registers and runs the
 // 21 taps once per phase with that phase's coefficients.
-template <typename T>
+template <typename T, int WL>
 __global__ void __launch_bounds__(64 * kChunk) k_colpass_adj_direct(const cx<T>* __restrict__ ghat,
                                                                    int64_t ghat_ev_stride,
                                                                    const cx<T>* __restrict__ rtick,
                                                                    cx<T>* __restrict__ hhat, int64_t hhat_ev_stride,
                                                                    int nw, int nphase, int nchunk, int ntile,
                                                                    int n_events) {
-  constexpr int K = kDirectK, NK = 2 * K + 1, WL = kDirectWL, WT = kDirectWT;
-  constexpr int SPAN = kDirectSpan, PSTR = kDirectPstr, C = kChunk;
+  using D = DirectTile<WL>;
+  constexpr int K = kDirectK, NK = 2 * K + 1, WT = D::WT, SPAN = D::SPAN, PSTR = D::PSTR, C = kChunk;
   constexpr int CPV = 16 / (int)sizeof(cx<T>);
   constexpr int VPW = C / CPV;
   constexpr int NE = SPAN * VPW;
@@ -239,39 +246,57 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_adj_direct(const cx<T>*
   }
 }
 
-namespace {
-template <typename T>
-size_t direct_lds() {
-  return sizeof(cx<T>) * 2 * kChunk * kDirectSubs * kSubPstr;
+// Output wires per lane of a launch: four below eight blocks of eight per CU (the adjoint,
+// whose block stages once, below four).  Blocks of eight
+// against four, us a plane: 157 blocks (256 wires, FP64) 31 and 24, 652 (600 wires, 2400 ticks)
+// 51 and 35, 1564 (800 wires, 6000 ticks) 115 and 108, 6255 (2400 wires, 9600 ticks) 390 and 405.
+static int direct_lanes(int nw, int nchunk, int n_events, int n_cu, int per_cu) {
+  const int64_t blocks = (int64_t)nchunk * n_events * ((nw + DirectTile<8>::WT - 1) / DirectTile<8>::WT);
+  return blocks < (int64_t)per_cu * n_cu ? 4 : 8;
 }
-}  // namespace
 
 bool colpass_direct_fits(int K) { return K == kDirectK; }
 
 // Dynamic LDS above the default 64 KB for the direct kernels (on the current device).
 void wiredirect_init_kernels() {
   const int lim = 160 * 1024 - 1024;
-  (void)hipFuncSetAttribute((const void*)k_colpass_direct<float>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void*)k_colpass_direct<double>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void*)k_colpass_adj_direct<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lim);
-  (void)hipFuncSetAttribute((const void*)k_colpass_adj_direct<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lim);
+  auto raise = [&](const void* f) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim); };
+  raise((const void*)k_colpass_direct<float, 8>);
+  raise((const void*)k_colpass_direct<double, 8>);
+  raise((const void*)k_colpass_direct<float, 4>);
+  raise((const void*)k_colpass_direct<double, 4>);
+  raise((const void*)k_colpass_adj_direct<float, 8>);
+  raise((const void*)k_colpass_adj_direct<double, 8>);
+  raise((const void*)k_colpass_adj_direct<float, 4>);
+  raise((const void*)k_colpass_adj_direct<double, 4>);
 }
 
 template <typename T>
 hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, const cx<T>* rtick, cx<T>* mhat,
-                                 int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, hipStream_t st,
-                                 const WireTiles& wt) {
+                                 int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, int n_cu,
+                                 hipStream_t st, const WireTiles& wt) {
   static_assert(kChunk == 4, "one wave per frequency of a chunk");
-  const int ntile = (nw + kDirectWT - 1) / kDirectWT;  // pairs of tiles
-  const int64_t nblk = (int64_t)nchunk * n_events * ntile;
-  if (nblk <= 0) return hipSuccess;
-  if (nblk > 0x7fffffff) return hipErrorInvalidValue;
-  const size_t lds = direct_lds<T>();  // FP64: above 64 KB, allowed by wiredirect_init_kernels
-  hipLaunchKernelGGL((k_colpass_direct<T>), dim3((unsigned)nblk), dim3(64 * kChunk), lds, st, shat, shat_ev_stride,
-                     rtick, mhat, mhat_ev_stride, nw, nphase, nchunk, ntile, n_events, wt);
-  return hipGetLastError();
+  hipError_t e = hipSuccess;
+  auto run = [&](auto wl) {
+    constexpr int WL = decltype(wl)::value;
+    using D = DirectTile<WL>;
+    const int ntile = (nw + D::WT - 1) / D::WT;  // blocks per (chunk, event): one or two tiles of the flags each
+    const int64_t nblk = (int64_t)nchunk * n_events * ntile;
+    if (nblk <= 0) return;
+    if (nblk > 0x7fffffff) {
+      e = hipErrorInvalidValue;
+      return;
+    }
+    const size_t lds = sizeof(cx<T>) * 2 * kChunk * D::SUBS * D::SUB_PSTR;  // FP64: above 64 KB (wiredirect_init_kernels)
+    hipLaunchKernelGGL((k_colpass_direct<T, WL>), dim3((unsigned)nblk), dim3(64 * kChunk), lds, st, shat,
+                       shat_ev_stride, rtick, mhat, mhat_ev_stride, nw, nphase, nchunk, ntile, n_events, wt);
+    e = hipGetLastError();
+  };
+  if (direct_lanes(nw, nchunk, n_events, n_cu, 8) == 4)
+    run(std::integral_constant<int, 4>());
+  else
+    run(std::integral_constant<int, 8>());
+  return e;
 }
 
 // One block per (event, tile): whether any impact row of the tile's wires, halo included,
@@ -330,25 +355,38 @@ hipError_t launch_reach(const WireTileGeom& g, int n_events, const uint32_t* bit
 
 template <typename T>
 hipError_t launch_colpass_adj_direct(const cx<T>* ghat, int64_t ghat_ev_stride, const cx<T>* rtick, cx<T>* hhat,
-                                     int64_t hhat_ev_stride, int nw, int nphase, int nchunk, int n_events,
+                                     int64_t hhat_ev_stride, int nw, int nphase, int nchunk, int n_events, int n_cu,
                                      hipStream_t st) {
-  const int ntile = (nw + kDirectWT - 1) / kDirectWT;
-  const int64_t nblk = (int64_t)nchunk * n_events * ntile;
-  if (nblk <= 0) return hipSuccess;
-  if (nblk > 0x7fffffff) return hipErrorInvalidValue;
-  const size_t lds = sizeof(cx<T>) * kChunk * kDirectPstr;
-  hipLaunchKernelGGL((k_colpass_adj_direct<T>), dim3((unsigned)nblk), dim3(64 * kChunk), lds, st, ghat,
-                     ghat_ev_stride, rtick, hhat, hhat_ev_stride, nw, nphase, nchunk, ntile, n_events);
-  return hipGetLastError();
+  hipError_t e = hipSuccess;
+  auto run = [&](auto wl) {
+    constexpr int WL = decltype(wl)::value;
+    using D = DirectTile<WL>;
+    const int ntile = (nw + D::WT - 1) / D::WT;
+    const int64_t nblk = (int64_t)nchunk * n_events * ntile;
+    if (nblk <= 0) return;
+    if (nblk > 0x7fffffff) {
+      e = hipErrorInvalidValue;
+      return;
+    }
+    hipLaunchKernelGGL((k_colpass_adj_direct<T, WL>), dim3((unsigned)nblk), dim3(64 * kChunk),
+                       sizeof(cx<T>) * kChunk * D::PSTR, st, ghat, ghat_ev_stride, rtick, hhat, hhat_ev_stride, nw,
+                       nphase, nchunk, ntile, n_events);
+    e = hipGetLastError();
+  };
+  if (direct_lanes(nw, nchunk, n_events, n_cu, 4) == 4)
+    run(std::integral_constant<int, 4>());
+  else
+    run(std::integral_constant<int, 8>());
+  return e;
 }
 
-template hipError_t launch_colpass_adj_direct<float>(const cx<float>*, int64_t, const cx<float>*, cx<float>*, int64_t,
-                                                     int, int, int, int, hipStream_t);
-template hipError_t launch_colpass_adj_direct<double>(const cx<double>*, int64_t, const cx<double>*, cx<double>*,
-                                                      int64_t, int, int, int, int, hipStream_t);
-template hipError_t launch_colpass_direct<float>(const cx<float>*, int64_t, const cx<float>*, cx<float>*, int64_t, int,
-                                                 int, int, int, hipStream_t, const WireTiles&);
-template hipError_t launch_colpass_direct<double>(const cx<double>*, int64_t, const cx<double>*, cx<double>*, int64_t,
-                                                  int, int, int, int, hipStream_t, const WireTiles&);
+#define WCT_DIRECT_INST(T)                                                                                          \
+  template hipError_t launch_colpass_adj_direct<T>(const cx<T>*, int64_t, const cx<T>*, cx<T>*, int64_t, int, int,  \
+                                                   int, int, int, hipStream_t);                                     \
+  template hipError_t launch_colpass_direct<T>(const cx<T>*, int64_t, const cx<T>*, cx<T>*, int64_t, int, int, int, \
+                                               int, int, hipStream_t, const WireTiles&);
+WCT_DIRECT_INST(float)
+WCT_DIRECT_INST(double)
+#undef WCT_DIRECT_INST
 
 }  // namespace wct
