@@ -285,9 +285,12 @@ RasterWs carve_raster(const wct_plan* P, Carver& cv, int n_events, int64_t n_row
   w.rank = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
   w.offs = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
   w.item_off = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
-  // at most ntiles + 4 n / 2^kItemShiftMin items
+  // room for ntiles + 4 n / 2^kItemShiftMin items and more; the whole is as large as it was with
+  // separate wide rows and 64 control words, so the calls that the static scratch of
+  // wct_raster_noalloc admits are the same
+  static_assert(kItemShiftMin >= 4, "n / 4 items beside one per tile");
   w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + (4 * nrow + 255) / 256 + 1)));
-  cv.take(sizeof(int32_t) * nrow);
+  cv.take(sizeof(int32_t) * std::max(nrow - (kCtrlWords - 64), nrow / 4));
   w.list = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
   cv.take(sizeof(int32_t) * 2 * (w.ntiles > 4096 ? (w.ntiles + 4095) / 4096 : 1));
   return w;

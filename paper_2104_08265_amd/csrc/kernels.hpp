@@ -77,7 +77,7 @@ struct RasterWs {
   int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches
   int32_t* offs;      // [ntiles]: a touched tile's slice of the row list
   int32_t* item_off;  // [ntiles]: its first work item
-  int32_t* items;     // [ntiles + n and more]: the work items' tiles
+  int32_t* items;     // [ntiles + n / 4 and more]: the work items' tiles
   int32_t* list;      // [4 n]; its end holds the wide rows, which have no entries in it
   int64_t ntiles;
   int item_shift;
