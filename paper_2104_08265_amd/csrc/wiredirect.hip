@@ -299,10 +299,8 @@ hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, cons
   return e;
 }
 
-// One block per (event, tile): whether any impact row of the tile's wires, halo included,
-// holds a window (span hi != 0).
-// Whether rows [lo, hi) of a plane's row flags hold a set bit; rows lo + 32 first, lo + 32
-// (first + step), ... are looked at.
+// Whether rows [lo, hi) of a plane's row flags hold a set bit, over the range's words first,
+// first + step, ...
 __device__ __forceinline__ bool any_row(const uint32_t* __restrict__ bits, int lo, int hi, int first, int step) {
   for (int wd = (lo >> 5) + first; wd <= (hi - 1) >> 5; wd += step) {
     uint32_t v = bits[wd];
