@@ -196,9 +196,10 @@ __global__ void __launch_bounds__(F::kThreads, F::kMinWaves) k_rows_r2c_pair_ct(
     return (f[(int64_t)c * nphase + i].y | f[(int64_t)(c + 1) * nphase + i].y) != 0;
   };
   // Whether a dead pair's zero spectrum is read: with row flags the direct column pass
-  // takes such rows as zeros, so it is never written; with tile flags alone only a live
-  // tile reads S^ (wires [t W - K, t W + W + K) of tile t), so a dead pair that no live
-  // tile covers is not written.
+  // takes such rows as zeros, so it is never written; with tile flags alone (more than 10
+  // phases) only a live tile reads S^ (wires [t W - K, t W + W + K) of tile t; a dead tile
+  // beside it in a block of that pass stages zeros), so a dead pair that no live tile covers
+  // is not written.
   auto pair_read = [&](int Q) -> bool {
     if (wt.rowbits) return false;  // the direct pass reads the rows no window reached as zeros
     if (!wt.live) return true;

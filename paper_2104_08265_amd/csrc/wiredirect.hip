@@ -44,7 +44,9 @@ struct DirectTile {
 // the current one is summed.  With tile flags the blocks take the tiles that some row
 // reaches, two by two, whatever lies between them, and the last blocks the others: bound by
 // its multiply-adds, the pass costs what the reached tiles do (16 sparse events, 41% of the
-// 256-wire tiles reached: 10.6 -> 7.8 ms; in whole 512-wire blocks, 51%).
+// 256-wire tiles reached: 10.6 -> 7.8 ms; in whole 512-wire blocks, 51%).  A tile no row
+// reaches never reads S^, of which pass A writes only what the reached tiles read: beside a
+// reached one in a block it is summed over zeros, so that its M^ is exactly 0.
 template <typename T, int WL>
 __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __restrict__ shat, int64_t shat_ev_stride,
                                                                const cx<T>* __restrict__ rtick, cx<T>* __restrict__ mhat,
@@ -67,28 +69,35 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
   // the block's tiles: the reached ones come first, then the others, each in order
   const int nsub = (nw + SW - 1) / SW;
   int sub[SUBS];
-  bool dead = false;
+  bool reached[SUBS];  // whether some row reaches the tile
 #pragma unroll
-  for (int b = 0; b < SUBS; ++b) sub[b] = SUBS * tile + b;
-  if (wt.live && nsub <= 64) {
+  for (int b = 0; b < SUBS; ++b) {
+    sub[b] = SUBS * tile + b;
+    reached[b] = sub[b] < nsub;
+  }
+  if (wt.live) {  // one flag per lane (at most 64 tiles: the launcher checks)
     const bool live = lane < nsub && wt.live[ev * wt.ev_stride + lane];
     const uint64_t m = __ballot(live), below = (1ull << lane) - 1ull;
     const int nlive = __popcll(m);
     const int place = lane >= nsub ? -1 : live ? __popcll(m & below) : nlive + lane - __popcll(m & below);
-    dead = SUBS * tile >= nlive;
 #pragma unroll
     for (int b = 0; b < SUBS; ++b) {
       const uint64_t who = __ballot(place == SUBS * tile + b);
       sub[b] = who ? __builtin_ctzll(who) : nsub;
+      reached[b] = SUBS * tile + b < nlive;
     }
   }
-  // first wire of each tile (past the grid, halo included, where there is none)
-  int w0s[SUBS];
+  // first output wire of each tile (past the grid where there is none), and the first wire that
+  // its staged ones surround (past the grid, halo included, where none is read)
+  int w0o[SUBS], w0s[SUBS];
 #pragma unroll
-  for (int b = 0; b < SUBS; ++b) w0s[b] = sub[b] < nsub ? sub[b] * SW : nw + K;
-  const int lsub = lane / SUB_LANES, w_lane = (lsub == 0 ? w0s[0] : w0s[SUBS - 1]) + WL * (lane % SUB_LANES);
+  for (int b = 0; b < SUBS; ++b) {
+    w0o[b] = sub[b] < nsub ? sub[b] * SW : nw;
+    w0s[b] = reached[b] ? w0o[b] : nw + K;
+  }
+  const int lsub = lane / SUB_LANES, w_lane = (lsub == 0 ? w0o[0] : w0o[SUBS - 1]) + WL * (lane % SUB_LANES);
   static_assert(SUBS <= 2, "a lane's tile is the first or the last");
-  if (dead) {  // no row reaches the tiles: M^ = 0
+  if (!reached[0] && !reached[SUBS - 1]) {  // no row reaches the tiles: M^ = 0
     if (wt.skip_dead) return;
     cx<T>* dst = mhat + ev * mhat_ev_stride;
     for (int o = 0; o < WL; ++o) {
@@ -276,6 +285,7 @@ hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, cons
                                  int64_t mhat_ev_stride, int nw, int nphase, int nchunk, int n_events, int n_cu,
                                  hipStream_t st, const WireTiles& wt) {
   static_assert(kChunk == 4, "one wave per frequency of a chunk");
+  if (wt.live && nw > 64 * kDirectTileWires) return hipErrorInvalidValue;  // (plans end at 5120 wires)
   hipError_t e = hipSuccess;
   auto run = [&](auto wl) {
     constexpr int WL = decltype(wl)::value;
