@@ -6,20 +6,29 @@
 //
 // A binomial count is the number of cumulative sums F(0), F(1), ... (in the order of the
 // search) that do not exceed the uniform u, so it is certain once u is further from every
-// sum than the estimates' error.  What the errors are, with e = 2^-24 (FP32 rounding):
-//  * p: the two FP64 weights rounded to FP32, their product, the division by N: 5 e
-//    relative, which moves a sum by at most N p pmf(k) 5 e <= 0.4 sqrt(N p) 5 e;
-//  * the first probability: inversion exp(N ln(1 - p)), an exponent of at most 14 (in
-//    base 2, 20) with 6 e relative error: 90 e; mode: a few e of a probability below 0.13;
-//  * each step's ratio: 6 e at most (the reciprocals of the hardware are within one unit
-//    in the last place); the sums weigh the k-th step's error by pmf(k): 6 e E[k] <= 60 e
-//    for the inversion, 6 e 0.8 sqrt(N p) for the search from the mode;
-//  * one rounding per subtraction from u: below e / 2 each, at most 30 that matter;
-//  * u: 19 of its 53 bits and half a unit of the last: 16 e;
-//  * p rounded to 17 bits of mantissa: 64 e relative, which moves a sum by at most
-//    26 e sqrt(N p).
-// Together below 206 e + 26 e sqrt(N p) = 1.8e-5 for the inversion and 50 e + 34 e sqrt(N p)
-// for the mode search; the margins are 2.5e-5 and 2.5e-5 + 4e-6 sqrt(N p).
+// sum than the estimates' error.  What the errors are, with e = 2^-24 (FP32 rounding, one
+// unit in the last place of the hardware's functions being 2 e), sums of worst cases:
+//  * the weights: the tile kernel takes them from the erf polynomial (erfpoly.hpp, a few
+//    1e-16), the definition from the alternating series det_erf, whose cancellation lets it
+//    be off by 5.2e-12 at the edges of 4.2-sigma windows (the sum of its terms' rounding
+//    bounds; measured at most 1.2e-13).  A weight is half a difference of two, the other
+//    axis' weight at most 1 and both together at most 3/2 below p = 1/2: N p is off by
+//    kWeightError N = 8e-12 N, and a sum by at most as much;
+//  * p: the two weights rounded to FP32, N times one, that times the other, the division by
+//    N: 6 e relative; then 17 bits of mantissa, 64 e; together 70 e, which moves a sum by
+//    at most 70 e N p pmf(k): 124 e for the inversion (N p pmf <= 1.77 at N = 20, p near
+//    1/2), 28 e s to 40 e s (p near 0 to 1/2) for the search from the mode, s = sqrt(N p);
+//  * the first probability: inversion exp(N ln(1 - p)), an exponent of at most 13.9 with
+//    9.5 e relative error: 134 e of every sum; mode: 12 e;
+//  * each step's ratio: inversion 6 e + 2 e (N + 1) / (N - k) (the difference of c1 / (k + 1)
+//    and r), weighed by pmf(k) over the steps at most 88 e; mode 10 e, 8 e s, and e j for
+//    the j subtractions behind the numerator of the j-th, e s^2 / 2;
+//  * one rounding per subtraction from u: at most 15 e, and 100 e for the long searches;
+//  * u: 19 of its 53 bits and half a unit of the last: 16 e; the definition's own rounding
+//    (its ln(n!) at N = 2^24): 3 e.
+// Together below 380 e + 8e-12 N = 2.27e-5 + 8e-12 N for the inversion, and for the mode
+// search 131 e + (36 e + e s / 2) s <= 131 e + 68 e s (s <= 64; near p = 1/2 131 e + 62 e s).
+// The margins are 2.5e-5 = 419 e and 2.5e-5 + 4e-6 s = 419 e + 67 e s, each with 8e-12 N.
 // Random inputs leave 0.05 to 0.2% of the cells undecided.
 #pragma once
 
@@ -64,12 +73,13 @@ constexpr int kFastSteps = 126;             // inversion steps at most
 constexpr int kFastUnrolled = 21;           // the first that is not unrolled (odd)
 constexpr int kFastPasses = 512;            // passes of the search from the mode at most
 constexpr float kFastMaxMean = 4096.0f;     // means up to which 512 passes hold eight widths
-constexpr float kFastMaxN = 67108864.0f;    // 2^26: above it the FP64 ln(n!) itself is only good to 1e-6
+constexpr float kFastMaxN = 16777216.0f;    // 2^24: up to it FP32 holds N and N - k exactly
+constexpr float kWeightError = 8e-12f;      // times N: error of N p from the weights
 
 // A cell surely draws 0 when u + N p is below this: 1 - N p is a lower bound of F(0), taken
-// with 1e-5 to spare.  Where p may exceed 1/2 the count runs down from N, not up from 0;
+// with 1e-5 and the weights' error to spare.  Where p may exceed 1/2 the count runs down from N, not up from 0;
 // then N p >= 3/2 for three electrons or more, so only rows of one or two are kept out.
-WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : 1.0f - 1e-5f; }
+WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : fmaf(N, -kWeightError, 1.0f - 1e-5f); }
 
 // A cell that waits for its batch, in 64 bits.  x: the probability, below 1/2 where it can be
 // decided (so its upper two bits are 0), to 17 bits of mantissa, over the row's index in the
@@ -123,8 +133,8 @@ WCT_HD void fast_steps(FastSearch& t) {
 
 // Inversion from 0 (N p < 10).  The lanes of a wave step together until none searches.
 WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
-  const float mu = N * p;
-  const bool fits = (mu < (float)kMuSwitch - 1e-4f) & (p < 0.4999f);
+  const float mu = N * p, werr = N * kWeightError;
+  const bool fits = (mu < (float)kMuSwitch - 1e-4f - werr) & (p < 0.4999f) & (N < kFastMaxN);
   // -ln(1 - p) = 2 atanh(p / (2 - p))
   const float s = p * fast_rcp(2.0f - p), s2 = s * s;
   float poly = 1.0f / 13.0f;
@@ -145,7 +155,8 @@ WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
     t.step(fast_rcp((float)j));
   }
   *count = t.k;
-  return fits & (t.near >= kDrawMargin) & (t.v < 0.0f);
+  // (the loops above end below kDrawMargin: a lane between the two margins is not sure)
+  return fits & (t.near >= kDrawMargin + werr) & (t.v < 0.0f);
 }
 
 // (1 + e) ln(1 + e) - e over e^2, |e| <= 0.1
@@ -170,16 +181,17 @@ WCT_HD float fast_stirling(float rn) {
 WCT_HD bool fast_chopdown(float N, float p, float u, int* count) {
   const float a = fmaf(N, p, p);  // (N + 1) p
   const float m = floorf(a), fr = a - m, mu = a - p;
-  const float tol = 6e-6f * a;  // p's error (68 e relative) decides the mode's floor
-  const bool fits = (fr > tol) & (fr < 1.0f - tol) & (p < 0.4999f) & (mu > (float)kMuSwitch + 1e-4f) & (mu < kFastMaxMean) &
-                    (N < kFastMaxN);
+  const float werr = N * kWeightError;
+  const float tol = fmaf(a, 6e-6f, werr);  // p's error (71 e relative, and the weights') decides the mode's floor
+  const bool fits = (fr > tol) & (fr < 1.0f - tol) & (p < 0.4999f) & (mu > (float)kMuSwitch + 1e-4f + werr) &
+                    (mu < kFastMaxMean) & (N < kFastMaxN);
   const float nm = N - m, nq = N - mu, q = 1.0f - p, x = p - fr;
   const float rN = fast_rcp(N), rm = fast_rcp(m), rnm = fast_rcp(nm);
   const float e1 = x * fast_rcp(mu), e2 = -x * fast_rcp(nq);
   const float dev = x * (e1 * fast_dev(e1) - e2 * fast_dev(e2));
   const float corr = fast_stirling(rN) - fast_stirling(rm) - fast_stirling(rnm) - dev;
   const float pm = fast_exp2(corr * (float)kLog2e) * fast_sqrt(N * (rm * rnm) * 0.15915494f);
-  const float margin = fmaf(kDrawMarginSigma, fast_sqrt(m), kDrawMargin);
+  const float margin = fmaf(kDrawMarginSigma, fast_sqrt(m), kDrawMargin) + werr;
   const float rp = p * fast_rcp(q), rq = q * fast_rcp(p);
   float v = fits ? u - pm : -1.0f;
   float near = fabsf(v), lo = pm, hi = pm;
@@ -235,12 +247,14 @@ WCT_HD bool fast_normal_pair(uint32_t w0, uint32_t w1, uint32_t w2, float* z_eve
 }
 
 // The normal mode's count: certain unless x = mu + sd z + 1/2 is within its error of a whole
-// number (mu: 6 e relative, sd: 4 e, z: 1.3e-5) or reaches the clamp at N.
+// number (mu: 6 e relative, sd: 4 e, z: 1.3e-5) or reaches the clamp at N.  The weights' error
+// of mu, d = kWeightError N, moves sd by d / (2 sd): below sd = 0.05 no |z| <= 8.6 takes x
+// away from 1/2 by as much as 0.44, above it x moves by at most d (1 + 8.6 / 0.1) < 100 d.
 WCT_HD bool fast_normal_count(float N, float mu, float p, float z, int* count) {
   const float sd = fast_sqrt(fmaxf(mu * (1.0f - p), 0.0f));
   const float x = fmaf(sd, z, mu) + 0.5f;
   const float fl = floorf(x), fr = x - fl;
-  const float margin = fmaf(sd, 3e-5f, fmaf(mu, 1e-6f, 2e-6f));
+  const float margin = fmaf(sd, 3e-5f, fmaf(mu, 1e-6f, fmaf(N, 100.0f * kWeightError, 2e-6f)));
   *count = (int)fmaxf(fl, 0.0f);
   return ((fr > margin) & (fr < 1.0f - margin) & (x < N)) | (x < -margin);
 }
