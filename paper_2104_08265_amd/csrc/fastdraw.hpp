@@ -81,9 +81,10 @@ constexpr float kWeightError = 8e-12f;      // times N: error of N p from the we
 // then N p >= 3/2 for three electrons or more, so only rows of one or two are kept out.
 WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : fmaf(N, -kWeightError, 1.0f - 1e-5f); }
 
-// A cell that waits for its batch, in 64 bits.  x: the probability, below 1/2 where it can be
-// decided (so its upper two bits are 0), to 17 bits of mantissa, over the row's index in the
-// work item; y: 19 bits of the uniform over the cell's offset in the tile.
+// A cell that waits for its batch, in 64 bits.  x: the probability in [0, 1] (its upper two bits
+// are then 0) to 17 bits of mantissa, over the row's index in the work item; y: 19 bits of the
+// uniform over the cell's offset in the tile.  Weights are below 0 and above 1 where the edges
+// round to five sigma: the definition counts 0 or N there; 0 is decided, 1 (and a NaN) left to it.
 constexpr uint32_t kEntryRow = 255u;
 constexpr int kEntryDstBits = 13;
 constexpr uint32_t kEntryDst = (1u << kEntryDstBits) - 1u;
@@ -101,7 +102,9 @@ WCT_HD float bits_float(uint32_t v) {
   return __builtin_bit_cast(float, v);
 #endif
 }
-WCT_HD uint32_t entry_x(float p, uint32_t row) { return (((float_bits(p) + 32u) << 2) & ~kEntryRow) | row; }
+WCT_HD uint32_t entry_x(float p, uint32_t row) {
+  return (((float_bits(fmaxf(fminf(p, 1.0f), 0.0f)) + 32u) << 2) & ~kEntryRow) | row;
+}
 WCT_HD uint32_t entry_y(uint32_t w, uint32_t dst) { return (w & ~kEntryDst) | dst; }
 WCT_HD float entry_p(uint32_t x) { return bits_float((x & ~kEntryRow) >> 2); }
 WCT_HD float entry_u(uint32_t y) { return (float)((y & ~kEntryDst) | (1u << (kEntryDstBits - 1))) * 0x1p-32f; }

@@ -2,7 +2,8 @@
 to 4.2 sigma: the estimates take the weights of the erf polynomial, the counts are defined by
 those of the series (det_erf), whose error grows towards the edges of wide windows and, times
 the electron count, passes any fixed margin.  Wherever the estimates claim certainty the count
-equals the oracle's, with uniforms next to the cumulative sums and up to 2^31 electrons."""
+equals the oracle's, with uniforms next to the cumulative sums and up to 2^31 electrons.  And
+where the series gives weights below 0 and above 1."""
 import os
 import shutil
 import subprocess
@@ -13,6 +14,8 @@ from scipy.special import erfinv
 
 from oracle import fluct as OF
 from oracle import normal as ON
+from test_fastdraw_host import binom
+from test_fastdraw_host import checker as plain_checker  # noqa: F401 (a fixture)
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -111,3 +114,13 @@ def test_sure_normal_counts_of_edge_cells(checker, nsigma, n_lo, n_hi):
     sure = assert_sure_counts(checker, "normal", ref, N, cell, *w[:3].astype(np.int64))
     if n_hi == 1e7:
         assert np.mean(sure) > 0.9
+
+
+def test_probabilities_outside_0_and_1(plain_checker):  # noqa: F811
+    rng = np.random.default_rng(34)
+    p = np.concatenate([-10.0 ** rng.uniform(-9, 4, 400), 10.0 ** rng.uniform(-0.5, 4, 400), [2.0, 4.0, -2.0]])
+    N, p, u = (v.ravel() for v in np.meshgrid([1, 2, 3, 20, 5000], p, [0.0, 0.1, 0.6, 0.9999], indexing="ij"))
+    sure, k = binom(plain_checker, N, p, u)
+    ref = OF.binomial(N, p, u)
+    bad = np.nonzero(sure & (k != ref))[0]
+    assert bad.size == 0, [(int(N[i]), float(p[i]), float(u[i]), int(k[i]), int(ref[i])) for i in bad[:5]]
