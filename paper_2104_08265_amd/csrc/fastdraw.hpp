@@ -250,16 +250,18 @@ WCT_HD bool fast_normal_pair(uint32_t w0, uint32_t w1, uint32_t w2, float* z_eve
 }
 
 // The normal mode's count: certain unless x = mu + sd z + 1/2 is within its error of a whole
-// number (mu: 6 e relative, sd: 4 e, z: 1.3e-5) or reaches the clamp at N.  The weights' error
+// number (mu: 6 e relative, sd: 14 e, z: 1.3e-5) or reaches the clamp at N.  The weights' error
 // of mu, d = kWeightError N, moves sd by d / (2 sd): below sd = 0.05 no |z| <= 8.6 takes x
 // away from 1/2 by as much as 0.44, above it x moves by at most d (1 + 8.6 / 0.1) < 100 d.
+// sd takes 1 - p: next to p = 1 (windows inside a cell) p's 6 e would be a large part of it, so
+// cells from p = 3/4 up are left to the defining computation (sd: 14 e below).
 WCT_HD bool fast_normal_count(float N, float mu, float p, float z, int* count) {
   const float sd = fast_sqrt(fmaxf(mu * (1.0f - p), 0.0f));
   const float x = fmaf(sd, z, mu) + 0.5f;
   const float fl = floorf(x), fr = x - fl;
   const float margin = fmaf(sd, 3e-5f, fmaf(mu, 1e-6f, fmaf(N, 100.0f * kWeightError, 2e-6f)));
   *count = (int)fmaxf(fl, 0.0f);
-  return ((fr > margin) & (fr < 1.0f - margin) & (x < N)) | (x < -margin);
+  return ((fr > margin) & (fr < 1.0f - margin) & (x < N) & (p < 0.75f)) | (x < -margin);
 }
 
 }  // namespace wct

@@ -116,6 +116,27 @@ def test_sure_normal_counts_of_edge_cells(checker, nsigma, n_lo, n_hi):
         assert np.mean(sure) > 0.9
 
 
+@pytest.mark.parametrize("nsigma", [3.0, 4.2])
+def test_sure_normal_counts_inside_one_cell(checker, nsigma):
+    """p = erf(nsigma / sqrt 2)^2, x next to whole numbers around N: sd rests on 1 - p."""
+    rng = np.random.default_rng(35)
+    N = np.exp(rng.uniform(np.log(20), np.log(20000), 100000)).astype(np.int64)
+    s = nsigma * SQRT_HALF
+    cell = [np.full(N.size, v) for v in (-s, s, -s, s)]
+    p = probability(cell)
+    sd = np.sqrt(N * p * (1.0 - p))
+    x = N - np.floor(np.abs(rng.normal(0, 1.5, N.size))) + rng.uniform(-3e-3, 3e-3, N.size) * np.maximum(sd, 0.05)
+    z = (x - 0.5 - N * p) / sd
+    ok = np.abs(z) < 6
+    N, z, cell = N[ok], z[ok], [c[ok] for c in cell]
+    w = np.zeros((4, N.size), np.uint64)  # the even cell's normal is r cos(0) or r cos(pi)
+    w[0] = (1.0 - np.exp(-0.5 * z * z)) * 2.0**32
+    w[1] = rng.integers(0, 2**32, N.size, dtype=np.uint64)
+    w[2] = np.where(z < 0, 2**31, 0)
+    ref = ON.normal_count(N, probability(cell), ON.box_muller_words(*w)[0])
+    assert_sure_counts(checker, "normal", ref, N, cell, *w[:3].astype(np.int64))
+
+
 def test_probabilities_outside_0_and_1(plain_checker):  # noqa: F811
     rng = np.random.default_rng(34)
     p = np.concatenate([-10.0 ** rng.uniform(-9, 4, 400), 10.0 ** rng.uniform(-0.5, 4, 400), [2.0, 4.0, -2.0]])
