@@ -69,35 +69,29 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
   // the block's tiles: the reached ones come first, then the others, each in order
   const int nsub = (nw + SW - 1) / SW;
   int sub[SUBS];
-  bool reached[SUBS];  // whether some row reaches the tile
+  bool dead = false, last = true;  // no row reaches the tiles; some row reaches the last of them
 #pragma unroll
-  for (int b = 0; b < SUBS; ++b) {
-    sub[b] = SUBS * tile + b;
-    reached[b] = sub[b] < nsub;
-  }
+  for (int b = 0; b < SUBS; ++b) sub[b] = SUBS * tile + b;
   if (wt.live) {  // one flag per lane (at most 64 tiles: the launcher checks)
     const bool live = lane < nsub && wt.live[ev * wt.ev_stride + lane];
     const uint64_t m = __ballot(live), below = (1ull << lane) - 1ull;
     const int nlive = __popcll(m);
+    dead = SUBS * tile >= nlive;
+    last = SUBS * tile + SUBS - 1 < nlive;
     const int place = lane >= nsub ? -1 : live ? __popcll(m & below) : nlive + lane - __popcll(m & below);
 #pragma unroll
     for (int b = 0; b < SUBS; ++b) {
       const uint64_t who = __ballot(place == SUBS * tile + b);
       sub[b] = who ? __builtin_ctzll(who) : nsub;
-      reached[b] = SUBS * tile + b < nlive;
     }
   }
-  // first output wire of each tile (past the grid where there is none), and the first wire that
-  // its staged ones surround (past the grid, halo included, where none is read)
-  int w0o[SUBS], w0s[SUBS];
+  // first wire of each tile (past the grid, halo included, where there is none)
+  int w0s[SUBS];
 #pragma unroll
-  for (int b = 0; b < SUBS; ++b) {
-    w0o[b] = sub[b] < nsub ? sub[b] * SW : nw;
-    w0s[b] = reached[b] ? w0o[b] : nw + K;
-  }
-  const int lsub = lane / SUB_LANES, w_lane = (lsub == 0 ? w0o[0] : w0o[SUBS - 1]) + WL * (lane % SUB_LANES);
+  for (int b = 0; b < SUBS; ++b) w0s[b] = sub[b] < nsub ? sub[b] * SW : nw + K;
+  const int lsub = lane / SUB_LANES, w_lane = (lsub == 0 ? w0s[0] : w0s[SUBS - 1]) + WL * (lane % SUB_LANES);
   static_assert(SUBS <= 2, "a lane's tile is the first or the last");
-  if (!reached[0] && !reached[SUBS - 1]) {  // no row reaches the tiles: M^ = 0
+  if (dead) {  // no row reaches the tiles: M^ = 0
     if (wt.skip_dead) return;
     cx<T>* dst = mhat + ev * mhat_ev_stride;
     for (int o = 0; o < WL; ++o) {
@@ -121,7 +115,7 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_direct(const cx<T>* __r
     __syncthreads();
   }
   auto row_live = [&](int b, int w, int i) {
-    if (!bits) return true;
+    if (!bits) return b < SUBS - 1 || last;  // (the flags know an unreached tile's rows)
     const int r = w * nphase + i;
     return ((s_bits[b * kBitWords + (r >> 5) - (b == 0 ? first_word(0) : first_word(SUBS - 1))] >> (r & 31)) & 1u) != 0;
   };
