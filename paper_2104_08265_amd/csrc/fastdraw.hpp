@@ -25,7 +25,9 @@
 //    the j subtractions behind the numerator of the j-th, e s^2 / 2;
 //  * one rounding per subtraction from u: at most 15 e, and 100 e for the long searches;
 //  * u: 19 of its 53 bits and half a unit of the last: 16 e; the definition's own rounding
-//    (its ln(n!) at N = 2^24): 3 e.
+//    (its ln(n!) at N = 2^24): 3 e;
+//  * N itself: exact below 2^24; above it (inversion only, p is then below 6e-7) up to 30 e in
+//    all, where the terms that grow with p are 70 e smaller.
 // Together below 380 e + 8e-12 N = 2.27e-5 + 8e-12 N for the inversion, and for the mode
 // search 131 e + (36 e + e s / 2) s <= 131 e + 68 e s (s <= 64; near p = 1/2 131 e + 62 e s).
 // The margins are 2.5e-5 = 419 e and 2.5e-5 + 4e-6 s = 419 e + 67 e s, each with 8e-12 N.
@@ -84,7 +86,8 @@ WCT_HD float fast_zero_limit(float N) { return N < 3.0f ? -INFINITY : fmaf(N, -k
 // A cell that waits for its batch, in 64 bits.  x: the probability in [0, 1] (its upper two bits
 // are then 0) to 17 bits of mantissa, over the row's index in the work item; y: 19 bits of the
 // uniform over the cell's offset in the tile.  Weights are below 0 and above 1 where the edges
-// round to five sigma: the definition counts 0 or N there; 0 is decided, 1 (and a NaN) left to it.
+// round to five sigma (no infinity, no NaN: they stay below 1e11); the definition counts 0 or N
+// there: 0 is decided, 1 left to it.
 constexpr uint32_t kEntryRow = 255u;
 constexpr int kEntryDstBits = 13;
 constexpr uint32_t kEntryDst = (1u << kEntryDstBits) - 1u;
@@ -103,7 +106,7 @@ WCT_HD float bits_float(uint32_t v) {
 #endif
 }
 WCT_HD uint32_t entry_x(float p, uint32_t row) {
-  return (((float_bits(fmaxf(fminf(p, 1.0f), 0.0f)) + 32u) << 2) & ~kEntryRow) | row;
+  return (((float_bits(fminf(fmaxf(p, 0.0f), 1.0f)) + 32u) << 2) & ~kEntryRow) | row;
 }
 WCT_HD uint32_t entry_y(uint32_t w, uint32_t dst) { return (w & ~kEntryDst) | dst; }
 WCT_HD float entry_p(uint32_t x) { return bits_float((x & ~kEntryRow) >> 2); }
@@ -136,8 +139,8 @@ WCT_HD void fast_steps(FastSearch& t) {
 
 // Inversion from 0 (N p < 10).  The lanes of a wave step together until none searches.
 WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
-  const float mu = N * p, werr = N * kWeightError;
-  const bool fits = (mu < (float)kMuSwitch - 1e-4f - werr) & (p < 0.4999f) & (N < kFastMaxN);
+  const float mu = N * p;
+  const bool fits = (fmaf(N, kWeightError, mu) < (float)kMuSwitch - 1e-4f) & (p < 0.4999f);
   // -ln(1 - p) = 2 atanh(p / (2 - p))
   const float s = p * fast_rcp(2.0f - p), s2 = s * s;
   float poly = 1.0f / 13.0f;
@@ -159,7 +162,7 @@ WCT_HD bool fast_inversion(float N, float p, float u, int* count) {
   }
   *count = t.k;
   // (the loops above end below kDrawMargin: a lane between the two margins is not sure)
-  return fits & (t.near >= kDrawMargin + werr) & (t.v < 0.0f);
+  return fits & (t.near >= fmaf(N, kWeightError, kDrawMargin)) & (t.v < 0.0f);
 }
 
 // (1 + e) ln(1 + e) - e over e^2, |e| <= 0.1
@@ -261,7 +264,7 @@ WCT_HD bool fast_normal_count(float N, float mu, float p, float z, int* count) {
   const float fl = floorf(x), fr = x - fl;
   const float margin = fmaf(sd, 3e-5f, fmaf(mu, 1e-6f, fmaf(N, 100.0f * kWeightError, 2e-6f)));
   *count = (int)fmaxf(fl, 0.0f);
-  return ((fr > margin) & (fr < 1.0f - margin) & (x < N) & (p < 0.75f)) | (x < -margin);
+  return (fr > margin) & (fr < 1.0f - margin) & (x < N) & (p < 0.75f);
 }
 
 }  // namespace wct
