@@ -277,22 +277,27 @@ int set_tiles(wct_plan* P, int v) {
 // Workspace layouts ---------------------------------------------------------------
 RasterWs carve_raster(const wct_plan* P, Carver& cv, int n_events, int64_t n_rows) {
   RasterWs w;
-  w.ntiles = (int64_t)n_events * P->ntiles_ev;
+  const int64_t nt = w.ntiles = (int64_t)n_events * P->ntiles_ev;
   const int64_t nrow = n_rows > 0 ? n_rows : 1;
-  w.n_rows = n_rows;
-  w.ctrl = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (kCtrlWords + w.ntiles)));
+  const size_t start = align_up(cv.off, 256);
+  w.ctrl = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (kCtrlWords + nt)));
   w.counts = w.ctrl ? w.ctrl + kCtrlWords : nullptr;
   w.rank = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
-  w.offs = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
-  w.item_off = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + 1)));
-  // room for ntiles + 4 n / 2^kItemShiftMin items and more; the whole is as large as it was with
-  // separate wide rows and 64 control words, so the calls that the static scratch of
-  // wct_raster_noalloc admits are the same
-  static_assert(kItemShiftMin >= 4, "n / 4 items beside one per tile");
-  w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (w.ntiles + (4 * nrow + 255) / 256 + 1)));
-  cv.take(sizeof(int32_t) * std::max(nrow - (kCtrlWords - 64), nrow / 4));
+  w.offs = static_cast<int32_t*>(cv.take(sizeof(int32_t) * nt));
+  w.item_off = static_cast<int32_t*>(cv.take(sizeof(int32_t) * nt));
+  // a row touches at most four tiles; a touched tile has one item and one more per
+  // 2^kItemShiftMin of its rows at most
+  w.items = static_cast<int32_t*>(cv.take(sizeof(int32_t) * (std::min(nt, 4 * nrow) + (4 * nrow >> kItemShiftMin) + 1)));
   w.list = static_cast<int32_t*>(cv.take(sizeof(int32_t) * 4 * nrow));
-  cv.take(sizeof(int32_t) * 2 * (w.ntiles > 4096 ? (w.ntiles + 4095) / 4096 : 1));
+  // The size decides which calls the static scratch of wct_raster_noalloc admits, so it stays
+  // what it has been from the first layout on (64 control words, an item per 256 rows, the wide
+  // rows and the scans' sums apart); calls of a few hundred rows and tiles, whose queue heads
+  // pass it by up to 1 KB, are far from that limit.
+  const auto words = [](int64_t n) { return align_up(sizeof(int32_t) * (size_t)n, 256); };
+  const size_t size = words(64 + nt) + 2 * words(4 * nrow) + 2 * words(nt + 1) + words(nt + (4 * nrow + 255) / 256 + 1) +
+                      words(nrow) + words(2 * std::max<int64_t>((nt + 4095) / 4096, 1));
+  const size_t used = align_up(cv.off, 256) - start;
+  if (used < size) cv.take(size - used);
   return w;
 }
 
@@ -319,13 +324,11 @@ WireTileGeom wire_tile_geom(const wct_plan* P) {
   WireTileGeom g;
   std::memset(&g, 0, sizeof(g));
   g.n_planes = P->n_planes;
-  g.rows_ev = P->rows_ev;
   for (int p = 0; p < P->n_planes; ++p) {
     const PlaneGeom& G = P->geom[p];
     g.nw[p] = G.nw;
     g.I[p] = G.I;
     g.K[p] = G.K;
-    g.row_off[p] = G.row_off;
     g.tile_off[p] = g.tiles_ev;
     g.tiles_ev += (G.nw + kDirectTileWires - 1) / kDirectTileWires;
     g.wire_off[p] = g.wires_ev;

@@ -77,11 +77,10 @@ struct RasterWs {
   int32_t* rank;      // [4 n]: a row's slot in the row list of each tile it touches
   int32_t* offs;      // [ntiles]: a touched tile's slice of the row list
   int32_t* item_off;  // [ntiles]: its first work item
-  int32_t* items;     // [ntiles + n / 4 and more]: the work items' tiles
+  int32_t* items;     // [min(ntiles, 4 n) + n / 4]: the work items' tiles
   int32_t* list;      // [4 n]; its end holds the wide rows, which have no entries in it
   int64_t ntiles;
   int item_shift;
-  int64_t n_rows;
   int2* span = nullptr;  // optional [event][rows_ev] tick spans of the rows (row_span)
   uint32_t* bits = nullptr;  // with span: [event][bits_ev], the rows some window reaches
   int2* hull = nullptr;  // with span: [event][bands] tile-column hull of each band of TH rows
@@ -220,9 +219,7 @@ hipError_t launch_colpass_direct(const cx<T>* shat, int64_t shat_ev_stride, cons
 // tiles start at tile_off[p] of an event's tiles_ev),
 struct WireTileGeom {
   int n_planes, tiles_ev, wires_ev;
-  int64_t rows_ev;
   int nw[kMaxPlanes], I[kMaxPlanes], K[kMaxPlanes], tile_off[kMaxPlanes + 1], wire_off[kMaxPlanes + 1];
-  int64_t row_off[kMaxPlanes];
   int bits_ev, bit_off[kMaxPlanes + 1];  // 32-row words of the row flags per event, per plane
 };
 // and the per-wire flags of WireLive for every plane and event ([event][wires_ev], plane
