@@ -31,22 +31,22 @@ TRAFFIC_JSON = os.path.join(PROFILES, "hbm_traffic.json")
 # The commands whose output --summarize reads (run from /tmp on the GPU host, R = repo root).
 PROFILE_COMMANDS = {
     "trace": "rocprofv3 --kernel-trace --stats -f csv -d $R/gpurun_out/prof_cfg2 -o cfg2 -- "
-             "python3 $R/bench.py --steps 5 --warmup 1 --no-cpu-baseline --no-extras --raster-tile 128x48x5 "
+             "python3 $R/bench.py --steps 5 --warmup 1 --no-cpu-baseline --no-extras --raster-tile 128x48 "
              "--tune-cache $R/gpurun_out/fft.tune",
     "fetch": "rocprofv3 --pmc FETCH_SIZE -f csv -d $R/gpurun_out/pmc_fetch -o fetch -- "
              "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --copy-calibration-mib 1024 "
-             "--raster-tile 128x48x5 --tune-cache $R/gpurun_out/fft.tune",
+             "--raster-tile 128x48 --tune-cache $R/gpurun_out/fft.tune",
     "write": "rocprofv3 --pmc WRITE_SIZE -f csv -d $R/gpurun_out/pmc_write -o write -- "
              "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --copy-calibration-mib 1024 "
-             "--raster-tile 128x48x5 --tune-cache $R/gpurun_out/fft.tune",
+             "--raster-tile 128x48 --tune-cache $R/gpurun_out/fft.tune",
     "trace_showers": "rocprofv3 --kernel-trace --stats -f csv -d $R/gpurun_out/prof_cfg3 -o cfg3 -- "
                      "python3 $R/bench.py --showers-only --steps 3",
     "sq": "rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_LDS SQ_INSTS_LDS_ATOMIC SQ_THREAD_CYCLES_VALU "
           "SQ_ACTIVE_INST_VALU SQ_WAVES SQ_LDS_BANK_CONFLICT -f csv -d $R/gpurun_out/pmc_sq -o sq -- "
-          "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --raster-tile 128x48x5 "
+          "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --raster-tile 128x48 "
           "--tune-cache $R/gpurun_out/fft.tune",
     "atomic": "rocprofv3 --pmc TCC_ATOMIC TCP_TOTAL_ATOMIC_WITHOUT_RET -f csv -d $R/gpurun_out/pmc_atomic -o atomic -- "
-              "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --raster-tile 128x48x5 "
+              "python3 $R/bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras --raster-tile 128x48 "
           "--tune-cache $R/gpurun_out/fft.tune",
 }
 COUNTERS_JSON = os.path.join(PROFILES, "raster_counters.json")
@@ -781,8 +781,8 @@ def main():
                     help="time only the shower workload (two faces, 1e6 depositions) and print its JSON")
     ap.add_argument("--summarize", metavar="DIR", help="write profiles/ summaries from rocprofv3 output in DIR")
     ap.add_argument("--tune-cache", metavar="FILE", help="transform-variant choices: read from / appended to FILE")
-    ap.add_argument("--raster-tile", metavar="RxTxB",
-                    help="use this raster tile shape (rows x ticks x blocks per CU) instead of the tuner's choice "
+    ap.add_argument("--raster-tile", metavar="RxT",
+                    help="use this raster tile shape (rows x ticks) instead of the tuner's choice "
                          "(the counter runs fix the shape their per-launch figures hold for)")
     ap.add_argument("--copy-calibration-mib", type=int, default=0,
                     help="first run 3 plain device copies of this many MiB (a known-size reference for "
@@ -818,8 +818,8 @@ def main():
     fft_choice = plan.tune(1, args.tune_cache)  # transform variant per plane and axis, timed on this GPU
     tiles = {v["index"]: v for v in wct.tile_variants()}
     if args.raster_tile:
-        want = tuple(int(x) for x in args.raster_tile.split("x"))
-        tile = next(i for i, v in tiles.items() if v["dtype"] == "f32" and (v["th"], v["tw"], v["blocks_per_cu"]) == want)
+        want = tuple(int(x) for x in args.raster_tile.split("x"))[:2]  # (a third number, blocks per CU, is passed over)
+        tile = next(i for i, v in tiles.items() if v["dtype"] == "f32" and (v["th"], v["tw"]) == want)
         plan.set_tile(tile)
     else:
         tile = plan.tune_raster(dd, o, args.tune_cache)  # raster tile shape, timed on this event's rows

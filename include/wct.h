@@ -357,7 +357,7 @@ int wct_plan_tune(wct_plan* plan, int32_t n_events, const char* cache_path, void
 /* Raster tile variants.  The raster accumulates each tile of TH impact rows x TW ticks in
  * LDS (Sec. 2.1.1 scatter adding through privatised tiles); the library compiles a few
  * shapes per dtype.  wct_tile_variant_info(idx, out[4]) fills out = {is_double, TH, TW,
- * tile-kernel blocks per CU} (HOST buffer).  A plan starts on the first variant of its
+ * blocks per CU of the binomial tile kernel} (HOST buffer).  A plan starts on the first variant of its
  * dtype; wct_plan_set_tile selects another (an index of the whole list, of the plan's
  * dtype, else WCT_E_INVALID) and wct_plan_get_tile reports it.  Every variant gives the
  * same grid (fluctuated: bit for bit).  The raster workspace depends on the variant:

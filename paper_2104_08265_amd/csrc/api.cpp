@@ -884,7 +884,7 @@ size_t tune_ws_bytes(const wct_plan* P, int n_events) {
 
 // Autotuning of the raster tile ---------------------------------------------------------
 // Cache line per (dtype, plane geometries, mean or fluctuated raster), e.g.
-//   wct-tile f32 3 2400 9600 10 2400 9600 10 3456 9600 10 fluct 1 -> 128 64 4
+//   wct-tile f32 3 2400 9600 10 2400 9600 10 3456 9600 10 fluct 1 -> 128 64 3
 std::string tile_key(const wct_plan* P, int fluctuate) {
   std::string k = std::string("wct-tile ") + (P->dtype == WCT_F32 ? "f32" : "f64") + " " + std::to_string(P->n_planes);
   for (const PlaneGeom& G : P->geom) k += " " + std::to_string(G.nw) + " " + std::to_string(G.nt) + " " + std::to_string(G.I);

@@ -41,8 +41,9 @@ constexpr int kQueues = 8, kQueueStride = 32;  // one queue per XCD, each head o
 constexpr int kItemShiftMin = 4, kItemShiftMax = 8;
 constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kernels at most
 
-// Raster tile variants: X(real type, TH rows, TW ticks, blocks per CU: part of a variant's name
-// in the tuner's cache; the tile kernels take what their LDS and registers admit).
+// Raster tile variants: X(real type, TH rows, TW ticks, blocks per CU of the binomial tile kernel:
+// what its LDS admits, checked where it is launched, and part of a variant's name in the tuner's
+// cache, so that a choice timed on a kernel of another occupancy is timed again).
 // Tall tiles: a window of up to 129 impact rows (sigma_p <= 2 pitches at 3 sigma) spans
 // at most 2 tile rows, so typical rows take the tile path.  TW is even (the tick pairs that
 // share a Philox block never straddle two tiles) and a multiple of 16 bytes (tiles are
@@ -51,12 +52,12 @@ constexpr int kZeroGroup = 16;     // tiles per clearing group of the tile kerne
 // but more rows straddle tiles.  The first variant of a type is a plan's default; the
 // raster tuner (wct_plan_tune_raster) times them on an event's rows.
 #define WCT_TILE_VARIANTS(X) \
-  X(float, 128, 48, 5)      \
-  X(float, 128, 64, 4)      \
-  X(float, 128, 32, 6)      \
+  X(float, 128, 48, 4)      \
+  X(float, 128, 64, 3)      \
+  X(float, 128, 32, 4)      \
   X(float, 256, 32, 3)      \
   X(double, 64, 64, 4)      \
-  X(double, 64, 32, 6)
+  X(double, 64, 32, 4)
 
 struct TileVariantDesc {
   int dbl;  // 0 float, 1 double

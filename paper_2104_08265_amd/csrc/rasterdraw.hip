@@ -481,6 +481,7 @@ hipError_t launch_tile_draw(const DepoView<T>& d, const RasterGeom& g, double ns
 }
 
 #define WCT_DRAW_INST(TT, TH_, TW_, OCC)                                                                            \
+  static_assert(draw_blocks<kModeBinomial, TH_, TW_>() == OCC, "blocks per CU of a tile variant");                   \
   template hipError_t launch_tile_draw<TT, TH_, TW_>(const DepoView<TT>&, const RasterGeom&, double, int, uint64_t, \
                                                      TT*, const RasterWs&, const DetTables*, const double*, int,    \
                                                      hipStream_t);
