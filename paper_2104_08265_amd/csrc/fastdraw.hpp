@@ -180,7 +180,8 @@ WCT_HD float fast_stirling(float rn) {
   return rn * fmaf(-r2, fmaf(-r2, 1.0f / 1260.0f, 1.0f / 360.0f), 1.0f / 12.0f);
 }
 
-// The search from the mode (N p >= 10).  P(mode) by the saddle-point form: with
+// The search from the mode (N p >= 10).  P(mode) by the saddle-point form (Loader, "Fast and
+// accurate computation of binomial probabilities", 2000): with
 // x = m - N p, ln P = S(N) - S(m) - S(N - m) - [N p h(x / N p) + N q h(-x / N q)]
 // - ln(2 pi m (N - m) / N) / 2, h(e) = (1 + e) ln(1 + e) - e, S the Stirling remainder:
 // no large terms cancel.

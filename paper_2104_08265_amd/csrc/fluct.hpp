@@ -180,7 +180,8 @@ WCT_HD double lfact_of(int64_t n, const double* __restrict__ lf, const Tab& tb) 
 // step below with a step above; p > 1/2 is drawn as N minus a draw with 1 - p.  The
 // cheap cases are decided first (binom_quick), the two searches are separate entry
 // points (binom_regime_draw), so that a caller can gather the cells of one regime and
-// run them together.  Lanes that run a search together share N (0 < N < 2^31):
+// run them together.  Lanes that run a search together may differ in N (0 < N < 2^31: each
+// lane's loop ends at its own cap); where they share it, N is uniform and its tests scalar:
 // integers enter the arithmetic as doubles kept up to date by exact +-1 steps, and in
 // the inversion every lane still searching has taken the same number of steps, so the
 // step's table entry is one shared read, issued two steps ahead.
@@ -230,7 +231,7 @@ WCT_HD bool any_lane(bool v) {
 template <typename Tab>
 WCT_HD int binom_inversion_shared(int N, double pp, double q, double u, const Tab& tb) {
   // q^N by left-to-right square-and-multiply: the leading bit of N gives q exactly, then
-  // each lower bit squares, and each set one multiplies by q (N is shared by the lanes, so
+  // each lower bit squares, and each set one multiplies by q (where N is shared by the lanes
   // the bit tests are scalar)
   double f = q;
   const int top = 31 - __builtin_clz((unsigned)N);

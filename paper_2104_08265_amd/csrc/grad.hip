@@ -18,7 +18,7 @@
 // down the impact rows (8 or 16 lanes side by side on consecutive ticks, as wastes fewer on the
 // window's width), three multiply-adds per cell where the direct sums take ten with two LDS
 // reads of three doubles each; the edges' erf and exponential are evaluated once per edge
-// instead of twice per cell.  Bound by the latency of H's short rows (13% of the vector issue
+// instead of twice per cell.  Bound by the latency of H's short rows (49% of the vector issue
 // slots, four waves per SIMD; five or more spill and are slower): 1.5e5 rows of 1400 cells
 // took 816 us, now 540 us.  Consecutive rows share an XCD's L2.  Sums in FP64, reduced across the wave.
 #include "convcommon.hpp"

@@ -94,9 +94,9 @@ __host__ __device__ inline int bands_before(const RasterGeom& g, int p) {
   return b;
 }
 
-// Tick span of an impact row as the raster records it: {kSpanBase - lo, hi}, both
-// raised by atomic max from zero, where [lo, hi) is the union hull of the tick windows of
-// the depositions that reach the row; {0, 0} when none does.  The row's samples outside
+// Tick span of an impact row as the raster records it (k_plan): {kSpanBase - lo, hi}, where
+// [lo, hi) holds the hull of the tiles that some deposition reaches in the row's band, if some
+// deposition's window reaches the row; else {0, 0}.  The row's samples outside
 // [lo, hi) are zero, so the row transform reads only inside it.
 constexpr int kSpanBase = 1 << 30;
 

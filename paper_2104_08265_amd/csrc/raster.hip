@@ -587,7 +587,11 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
 // 7220 for 1024 blocks and would end 1.47 times later than with the work dealt out evenly
 // (items of 64 rows 1.22), an event of 6000 rows on one track 95 items, 23 times (16 rows:
 // 2.5).  Smaller items cost more tile writes by atomics.  So: about the rows a CU has in
-// 1/64 of the call, between 16 and 256.
+// 1/64 of the call, between 16 and 256; of the mean raster, whose rows cost a tenth beside the
+// same writes, in 1/8 (in 1/64 the track event's mean raster took 1100 us instead of 840).
+// n counts all rows of a call: wct_simulate over several sub-batches (more events than
+// max_events) rasters only a sub-batch's events at a time, whose rows the host does not know, so
+// their items are larger than such events alone would get, and never larger than 256 rows.
 static int item_shift(int64_t n, int mode, int n_cu) {
   int s = kItemShiftMin;
   while (s < kItemShiftMax && ((int64_t)(mode == kModeMean ? 8 : 64) * n_cu << s) < n) ++s;

@@ -250,9 +250,17 @@ __global__ void __launch_bounds__(64 * kChunk) k_colpass_adj_direct(const cx<T>*
 }
 
 // Output wires per lane of a launch: four below eight blocks of eight per CU (the adjoint,
-// whose block stages once, below four).  Blocks of eight
-// against four, us a plane: 157 blocks (256 wires, FP64) 31 and 24, 652 (600 wires, 2400 ticks)
-// 51 and 35, 1564 (800 wires, 6000 ticks) 115 and 108, 6255 (2400 wires, 9600 ticks) 390 and 405.
+// whose block stages once, below four).  Blocks of eight against four, us a plane (dense, FP32,
+// n events of a plane): forward, 256 wires 1256 blocks 73 and 44, 2512 140 and 81; 600 wires
+// 676 52 and 37, 2028 119 and 91, 2704 159 and 119; 800 wires 1564 106 and 99, 3128 187 and 183,
+// 4692 268 and 266, 6256 351 and 351; 2400 wires 6255 355 and 354.  With the flags of a sparse
+// event eight are ahead on large launches (three planes, 6255 to 9000 blocks, whole call 5825
+// against 5870 us).  Adjoint, 256 wires 1256 blocks 69 and 65, 2512 128 and 123; 600 wires 676
+// 54 and 46, 1352 98 and 82, 2028 133 and 123; 800 wires 1564 136 and 151, 3128 264 and 293;
+// 1000 wires 676 69 and 73, 2028 185 and 194; 2400 wires 560 and 584.  The lines are not where
+// every dense plane would put them: a plane whose last 512 wires are at most half there (256,
+// 600 wires) pays 1.2 to 1.8 times past them for the lanes it pads, the others at most 6% on
+// either side.
 static int direct_lanes(int nw, int nchunk, int n_events, int n_cu, int per_cu) {
   const int64_t blocks = (int64_t)nchunk * n_events * ((nw + DirectTile<8>::WT - 1) / DirectTile<8>::WT);
   return blocks < (int64_t)per_cu * n_cu ? 4 : 8;
