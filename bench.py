@@ -394,22 +394,6 @@ def cpu_baseline(wl, n_sample_depos=3000):
     }
 
 
-def window_cells(wl, nsigma=3.0):
-    """Cells of all rows' truncated windows inside the grid: the mean raster's LDS adds
-    (one per cell; rows wider than four tiles excepted, a small share)."""
-    import numpy as np
-    d = wl.depos
-    total = 0
-    for k, pl in enumerate(wl.planes):
-        m = np.asarray(d.plane) == k
-        u, su = pl.n_impacts * np.asarray(d.p, np.float64)[m], pl.n_impacts * np.asarray(d.sigma_p, np.float64)[m]
-        t, st = np.asarray(d.t, np.float64)[m], np.asarray(d.sigma_t, np.float64)[m]
-        nb = np.minimum(np.ceil(u + nsigma * su), pl.n_impacts * pl.n_wires) - np.maximum(np.floor(u - nsigma * su), 0)
-        nt = np.minimum(np.ceil(t + nsigma * st), pl.n_ticks) - np.maximum(np.floor(t - nsigma * st), 0)
-        total += int(np.sum(np.clip(nb, 0, None) * np.clip(nt, 0, None)))
-    return total
-
-
 def cpu_parallel_baseline(wl, n_sample_rows=30000):
     """A CPU-parallel leg on this host's cores: the fluctuated raster vectorised in NumPy
     (window weights by scipy's erf, counts by NumPy's binomial generator, scatter-add by
@@ -662,19 +646,15 @@ def issue_rates(wct):
     return out
 
 
-def raster_atomics(wct, wl, t_mean_ms, t_fluct_ms, tile=None):
-    """The raster's atomic adds against the chip's peaks (the probes): the mean raster makes
-    one LDS add per window cell (counted on the host); the fluctuated raster's LDS and
-    device-memory atomic instructions come from the committed counters of this build."""
+def raster_atomics(wct, t_fluct_ms, tile=None):
+    """The fluctuated raster's atomic adds (32-bit integer ones in LDS, floating-point ones in
+    device memory where a tile is split; from the committed counters of this build) against the
+    floating-point peaks of the probes.  The mean raster sums in registers."""
     lds_peak, _ = wct.probe_atomic_add("lds", blocks=2048, iters=256)
     glob_peak, _ = wct.probe_atomic_add("global", blocks=2048, iters=32, buf_elems=2048 * 256 * 2)
     out = {"lds_peak_adds_per_s": lds_peak, "global_peak_adds_per_s": glob_peak,
            "probe": "wct_probe_atomic_add: 2048 blocks x 256 threads, a wave's 64 lanes on 64 consecutive floats; "
                     "device-memory adds over a 4 MiB buffer (L2)"}
-    if t_mean_ms:
-        cells = window_cells(wl)
-        rate = cells / (t_mean_ms * 1e-3)
-        out["mean_raster"] = {"lds_adds": cells, "ms": t_mean_ms, "adds_per_s": rate, "frac_of_lds_peak": rate / lds_peak}
     c = measured_counters("raster_tile_fluct", tile)
     if c and t_fluct_ms:
         lds_i = c["SQ_INSTS_LDS_ATOMIC"]
@@ -846,21 +826,24 @@ def main():
     torch.cuda.synchronize()
     ms = ev0.elapsed_time(ev1) / args.steps
     kt = plan.profile_read()
-    # after the timed region: the mean raster of the same event (its LDS adds for the
-    # atomic-throughput evidence), the normal-approximation raster (Box-Muller mode), then
-    # the same step with noise added
-    plan.profile_reset()
-    plan.raster(dd, wct.opts(wl.nsigma, False, 1, wl.seed))
-    torch.cuda.synchronize()
-    t_mean = plan.profile_read().get("raster_tile_mean", (None, 0))[0]
-    o_norm = wct.opts(wl.nsigma, wct.FLUCT_NORMAL, 1, wl.seed)
-    plan.raster(dd, o_norm)
-    plan.profile_reset()
-    for _ in range(3):
-        plan.raster(dd, o_norm)
-    torch.cuda.synchronize()
-    t_normal = plan.profile_read().get("raster_tile_normal", (None, 0))[0]
-    t_normal = t_normal / 3 if t_normal is not None else None
+    # after the timed region: the mean raster of the same event and the normal-approximation
+    # raster (Box-Muller mode), three launches each after one, on a grid whose pages are there;
+    # then the same step with noise added
+    grid = plan.new_grid(1)
+
+    def tile_ms(mode, name):
+        om = wct.opts(wl.nsigma, mode, 1, wl.seed)
+        plan.raster(dd, om, grid)
+        plan.profile_reset()
+        for _ in range(3):
+            plan.raster(dd, om, grid)
+        torch.cuda.synchronize()
+        t, n = plan.profile_read().get(name, (None, 0))
+        return t / n if n else None
+
+    t_mean = tile_ms(wct.FLUCT_MEAN, "raster_tile_mean")
+    t_normal = tile_ms(wct.FLUCT_NORMAL, "raster_tile_normal")
+    del grid
     plan.profile(False)
     noise = noise_cost(wct, synth, plan, dd, wl, wave)
     adc = adc_cost(plan, wave)
@@ -887,7 +870,7 @@ def main():
     t_conv = sum(v["ms_per_step"] for k, v in kernels.items() if k in ("rows_r2c", "colpass", "rows_c2r"))
     dom = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
     # roofline of the dominant kernel: the fluctuated raster is bound by lane arithmetic
-    # (Philox products and the FP64 sampler), the transform passes by HBM
+    # (Philox products and the searches of the counts), the transform passes by HBM
     fft_dom = max(("rows_r2c", "colpass", "rows_c2r"), key=lambda k: kernels.get(k, {}).get("ms_per_step", 0))
     kd = kernels[fft_dom]
     roofline_fft = {"kernel": fft_dom, "bound": "hbm", "achieved": kd["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -937,7 +920,7 @@ def main():
         "roofline_fft": roofline_fft,
         "fft_plans": fft_desc,
         "raster_tile": tile_shape,
-        "raster_atomics": raster_atomics(wct, wl, t_mean, kernels.get("raster_tile_fluct", {}).get("ms_per_step"),
+        "raster_atomics": raster_atomics(wct, kernels.get("raster_tile_fluct", {}).get("ms_per_step"),
                                          tile_shape),
         "raster_issue": raster_issue(kernels.get("raster_tile_fluct", {}).get("ms_per_step"),
                                      roofline.get("alg_ops_per_launch"), tile_shape),
